@@ -60,7 +60,7 @@ template <class C> struct Moments {
 template <class C> struct Pre {
     C rho, u[3];  // u: velocity inside the equilibrium (PR: j/rho; IR: j/rho + g/2)
     C a[6];       // IR: post-collision stress tensor A = lambda dev(T)
-    C tau_p, tau_m, nu_app, gamma, Tn;
+    C tau_p, tau_m, om_m, nu_app, gamma, Tn;
     bool unyielded, near_yield;
 };
 
@@ -105,10 +105,81 @@ __device__ __forceinline__ Moments<C> moments_as(const H (&h)[Lattice<LAT>::Q])
     return mo;
 }
 
+// Classes of velocities: face pairs 1 + 2 a along axis a; in each plane (a, b)
+// of axes (x y, then x z and y z in 3-D) the edge pairs +a+b and +a-b; in
+// D3Q27 the corner pairs +++, ++-, +-+, -++.  FP64 forms moments and
+// post-collision values class by class: the sums that a plane's or the
+// corners' pairs share are taken once, and the weight is the class's (D3Q27:
+// 81 operations for the moments and 110 for IR's post-collision values, where
+// the direction-wise form takes 137 and 190; TRT 160 for 364).  Rounding
+// differs from the direction-wise form at 1e-15; FP32 and FP16 keep that one
+// and with it their states bit for bit (there the class form gained 1 to 3%,
+// their kernels being bound by memory).
+template <int LAT> constexpr int kPlanes = Lattice<LAT>::D == 3 ? 3 : 1;
+template <int LAT> constexpr int edge0(int plane) { return (Lattice<LAT>::D == 3 ? 7 : 5) + 4 * plane; }
+constexpr int plane_a(int p) { return p == 2 ? 1 : 0; }
+constexpr int plane_b(int p) { return p == 0 ? 1 : 2; }
+constexpr int kCorner0 = 19;
+
+template <int LAT, class C>
+__device__ __forceinline__ Moments<C> moments_by_class(const C (&h)[Lattice<LAT>::Q])
+{
+    using L = Lattice<LAT>;
+    constexpr int D = L::D;
+    Moments<C> mo;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) mo.j[a] = 0;
+#pragma unroll
+    for (int a = 0; a < 6; ++a) mo.p[a] = 0;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        mo.p[a] = h[1 + 2 * a] + h[2 + 2 * a];
+        mo.j[a] = h[1 + 2 * a] - h[2 + 2 * a];
+    }
+    C all = mo.p[0] + mo.p[1];  // sum over the moving velocities
+    if (D == 3) all += mo.p[2];
+#pragma unroll
+    for (int e = 0; e < kPlanes<LAT>; ++e) {
+        const int i = edge0<LAT>(e), a = plane_a(e), b = plane_b(e);
+        const C sp = h[i] + h[i + 1], dp = h[i] - h[i + 1];
+        const C sm = h[i + 2] + h[i + 3], dm = h[i + 2] - h[i + 3];
+        const C both = sp + sm;
+        mo.p[a] += both;
+        mo.p[b] += both;
+        all += both;
+        mo.p[3 + e] = sp - sm;
+        mo.j[a] += dp + dm;
+        mo.j[b] += dp - dm;
+    }
+    if constexpr (L::Q == 27) {
+        constexpr int i = kCorner0;
+        const C s1 = h[i] + h[i + 1], d1 = h[i] - h[i + 1];          // + + +
+        const C s2 = h[i + 2] + h[i + 3], d2 = h[i + 2] - h[i + 3];  // + + -
+        const C s3 = h[i + 4] + h[i + 5], d3 = h[i + 4] - h[i + 5];  // + - +
+        const C s4 = h[i + 6] + h[i + 7], d4 = h[i + 6] - h[i + 7];  // - + +
+        const C s12 = s1 + s2, t12 = s1 - s2, s34 = s3 + s4, t34 = s3 - s4;
+        const C four = s12 + s34;
+        mo.p[0] += four;
+        mo.p[1] += four;
+        mo.p[2] += four;
+        all += four;
+        mo.p[3] += s12 - s34;
+        mo.p[4] += t12 + t34;
+        mo.p[5] += t12 - t34;
+        const C d12 = d1 + d2, d34 = d3 - d4;
+        mo.j[0] += d12 + d34;
+        mo.j[1] += d12 - d34;
+        mo.j[2] += (d1 - d2) + (d3 + d4);
+    }
+    mo.drho = all + h[0];
+    return mo;
+}
+
 template <int LAT, class C>
 __device__ __forceinline__ Moments<C> moments(const C (&h)[Lattice<LAT>::Q])
 {
-    return moments_as<LAT, C, C>(h);
+    if constexpr (sizeof(C) == 8) return moments_by_class<LAT, C>(h);
+    else return moments_as<LAT, C, C>(h);
 }
 
 // Non-equilibrium second moment Pi - rho cs^2 I - rho v v, from the
@@ -286,6 +357,8 @@ __device__ __forceinline__ Pre<C> rheology(const Moments<C>& mo, const Coll<C>& 
         r.gamma = gamma;
         r.tau_p = C(0.5) + C(3) * nu;
         r.tau_m = C(0.5) + p.lambda / (r.tau_p - C(0.5));
+        // 1 / tau_m, with tau_p - 1/2 = 3 nu
+        r.om_m = sizeof(C) == 8 ? (C(3) * nu) / (C(1.5) * nu + p.lambda) : C(1) / r.tau_m;
         // the regularised stress magnitude sqrt(sigma:sigma / 2) = rho nu gamma
         // against the yield stress: unyielded below it, redone in FP64 (when
         // enabled) within the band around it
@@ -303,7 +376,7 @@ __device__ __forceinline__ Pre<C> rheology(const Moments<C>& mo, const Coll<C>& 
         if (p.axis == 2) t[1] = C(0);
         if (p.axis == 3) t[2] = C(0);
         const C tr = (D == 3) ? t[0] + t[1] + t[2] : t[0] + t[1];
-        const C trd = tr / C(D);
+        const C trd = sizeof(C) == 8 ? tr * (C(1) / C(D)) : tr / C(D);
         t[0] -= trd;
         t[1] -= trd;
         if (D == 3) t[2] -= trd;
@@ -320,11 +393,100 @@ __device__ __forceinline__ Pre<C> rheology(const Moments<C>& mo, const Coll<C>& 
         r.unyielded = !yielded;
         r.near_yield = p.sigma_y > C(0) && fabs(Tn - p.sqrt2_sy) < p.band * p.sqrt2_sy;
         r.tau_p = tau_prev;
-        r.tau_m = tau_prev;
+        r.tau_m = r.om_m = tau_prev;
         r.nu_app = p.nu_p;
         r.gamma = 0;
     }
     return r;
+}
+
+// Values of an even quadratic form and an odd linear form on the velocities:
+// visit(i, E, O) is called for each opposite pair (i, i + 1) with E = e0 + M :
+// c c and O = B . c, c the velocity i; m holds xx, yy, zz and twice xy, xz, yz.
+template <int LAT, class C, class F>
+__device__ __forceinline__ void pair_forms(C e0, const C (&m)[6], const C (&v)[3], F&& visit)
+{
+    using L = Lattice<LAT>;
+#pragma unroll
+    for (int a = 0; a < L::D; ++a) visit(1 + 2 * a, e0 + m[a], v[a]);
+#pragma unroll
+    for (int p = 0; p < kPlanes<LAT>; ++p) {
+        const int i = edge0<LAT>(p), a = plane_a(p), b = plane_b(p);
+        const C base = e0 + (m[a] + m[b]);
+        visit(i, base + m[3 + p], v[a] + v[b]);
+        visit(i + 2, base - m[3 + p], v[a] - v[b]);
+    }
+    if constexpr (L::Q == 27) {
+        const C base = e0 + (m[0] + m[1] + m[2]);
+        const C up = base + m[3], dn = base - m[3];
+        const C zp = m[4] + m[5], zm = m[4] - m[5];
+        const C vp = v[0] + v[1], vm = v[0] - v[1];
+        visit(kCorner0, up + zp, vp + v[2]);      // + + +
+        visit(kCorner0 + 2, up - zp, vp - v[2]);  // + + -
+        visit(kCorner0 + 4, dn + zm, vm + v[2]);  // + - +
+        visit(kCorner0 + 6, dn - zm, v[2] - vm);  // - + +
+    }
+}
+
+// Relaxation class by class (TRT and IR; see relax).
+//  TRT: the EDM difference is absorbed in the state relaxed to: with E and O the
+//   even and odd parts of h_eq + tau (f_eq(u + g) - f_eq(u)) (tau_p for the
+//   even, tau_m for the odd part), h_i += om_p (E - even) + om_m (O - odd), the
+//   changes small against h_i.
+template <int LAT, int OP, class C>
+__device__ __forceinline__ void relax_by_class(C (&h)[Lattice<LAT>::Q], const Moments<C>& mo, const Pre<C>& r,
+                                               const Coll<C>& p)
+{
+    using L = Lattice<LAT>;
+    const C* u = r.u;
+    const C rho15 = C(1.5) * r.rho, rho45 = C(4.5) * r.rho, rho3 = C(3) * r.rho;
+    if constexpr (pr_family(OP)) {
+        const C om_p = C(1) / r.tau_p;
+        C tg[3], s[3], B[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            tg[a] = r.tau_p * p.g[a];
+            s[a] = u[a] + p.g[a];
+            B[a] = rho3 * (u[a] + r.tau_m * p.g[a]);
+        }
+        // u u + tau_p (u g + g u + g g)
+        const C q0 = u[0] * (u[0] + tg[0]) + tg[0] * s[0];
+        const C q1 = u[1] * (u[1] + tg[1]) + tg[1] * s[1];
+        const C q2 = u[2] * (u[2] + tg[2]) + tg[2] * s[2];
+        const C rho9 = C(9) * r.rho;
+        const C M[6] = {rho45 * q0, rho45 * q1, rho45 * q2,
+                        rho9 * (u[0] * (u[1] + tg[1]) + tg[0] * s[1]),
+                        rho9 * (u[0] * (u[2] + tg[2]) + tg[0] * s[2]),
+                        rho9 * (u[1] * (u[2] + tg[2]) + tg[1] * s[2])};
+        const C e0 = mo.drho - rho15 * (q0 + q1 + q2);
+        h[0] += om_p * (C(L::w[0]) * e0 - h[0]);
+        const C hp = C(0.5) * om_p, hm = C(0.5) * r.om_m;
+        pair_forms<LAT>(e0, M, B, [&](int i, C E, C O) {
+            const C w2 = C(2 * L::w[i]);
+            C hi = h[i], hk = h[i + 1];
+            // form the pair's sum and difference again instead of holding those
+            // of the moments (two registers each per pair); no instruction
+            asm("" : "+v"(hi), "+v"(hk));
+            const C x = hp * (w2 * E - (hi + hk)), y = w2 * O - (hi - hk);
+            h[i] = hi + (x + hm * y);
+            h[i + 1] = hk + (x - hm * y);
+        });
+    } else {
+        const C* A = r.a;
+        const C uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+        const C ru[3] = {rho45 * u[0], rho45 * u[1], rho45 * u[2]};
+        const C M[6] = {ru[0] * u[0] + C(4.5) * A[0], ru[1] * u[1] + C(4.5) * A[1], ru[2] * u[2] + C(4.5) * A[2],
+                        C(2) * (ru[0] * u[1] + C(4.5) * A[3]), C(2) * (ru[0] * u[2] + C(4.5) * A[4]),
+                        C(2) * (ru[1] * u[2] + C(4.5) * A[5])};
+        const C B[3] = {rho3 * u[0] + rho15 * p.g[0], rho3 * u[1] + rho15 * p.g[1], rho3 * u[2] + rho15 * p.g[2]};
+        const C e0 = mo.drho - rho15 * uu - C(1.5) * (A[0] + A[1] + A[2]);
+        h[0] = C(L::w[0]) * e0;
+        pair_forms<LAT>(e0, M, B, [&](int i, C E, C O) {
+            const C w = C(L::w[i]), wo = w * O;
+            h[i] = w * E + wo;
+            h[i + 1] = w * E - wo;
+        });
+    }
 }
 
 // Relaxation: overwrite h with the post-collision deviations.
@@ -338,12 +500,16 @@ template <int LAT, int OP, class C, class H>
 __device__ __forceinline__ void relax(H (&h)[Lattice<LAT>::Q], const Moments<C>& mo, const Pre<C>& r,
                                       const Coll<C>& p)
 {
+    if constexpr (sizeof(H) == 8 && !is_mrt(OP)) {
+        relax_by_class<LAT, OP>(h, mo, r, p);
+        return;
+    }
     using L = Lattice<LAT>;
     const C* u = r.u;
     const C uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
     if (pr_family(OP)) {
         const C om_p = C(1) / r.tau_p;
-        const C om_m = C(1) / r.tau_m;
+        const C om_m = r.om_m;
         // MRT (Sec. 2.1): with the weights' inner product the second-order
         // Hermite projection of h - h_eq splits into shear (cc : Pi_dev) and
         // bulk ((tr/d)(|c|^2 - d cs^2)) parts; the remaining even moments take
