@@ -267,14 +267,56 @@ __device__ __forceinline__ float d_pow(float b, float e) { return powf(b, e); }
 // step would leave it) from the n = 1 closed form (exact for Bingham), until
 // a step falls below the precision's resolution.  A bound that underflows
 // to zero returns zero (s is then negligible against Tn).
+//
+// In FP64 the search starts from a root found in single precision by the same
+// rule (fast base-2 powers), good to about 1e-6, and ends with the first step
+// below 1e-9 x: Newton's error after a step d is about (n - 1)/2 (d/x)^2 x, so
+// that step lands within 1e-17 of the root.  Two evaluations of the FP64 power
+// instead of six or seven (one of them for the bound).
+__device__ __forceinline__ float fast_powf(float b, float e) { return __builtin_amdgcn_exp2f(e * __builtin_amdgcn_logf(b)); }
+
+__device__ __forceinline__ float hb_start(float e, float c, float n)
+{
+    float lo = 0.0f, hi = fminf(2.0f * e, fast_powf(e / c, 1.0f / n) * 1.0001f);
+    float x = fminf(e / (0.5f + c), hi);
+    for (int it = 0; it < 12; ++it) {
+        const float xn1 = fast_powf(x, n - 1.0f);
+        const float F = 0.5f * x + c * xn1 * x - e;
+        if (F > 0.0f) hi = x;
+        else lo = x;
+        const float step = F / (0.5f + c * n * xn1);
+        float xn = x - step;
+        const bool conv = fabsf(step) <= 3e-6f * x;
+        if (!conv && !(xn > lo && xn < hi)) xn = 0.5f * (lo + hi);
+        x = xn;
+        if (conv) break;
+    }
+    return x;
+}
+
 template <class C>
 __device__ __forceinline__ C hb_moment(C Tn, const Coll<C>& p)
 {
     const C e = Tn - p.sqrt2_sy;
-    C lo = C(0), hi = fmin(C(2) * e, d_pow(e / p.hb_c, C(1) / p.hb_n));
-    if (!(hi > C(0))) return C(0);
-    C x = fmin(e / (C(0.5) + p.hb_c), hi);
+    C lo = C(0), hi, x;
     const C tol = sizeof(C) == 8 ? C(1e-14) : C(2e-7);
+    const C last = sizeof(C) == 8 ? C(1e-9) : tol;  // a step this small ends the search
+    if constexpr (sizeof(C) == 8) {
+        hi = C(2) * e;
+        if (!(hi > C(0))) return C(0);
+        x = (C)hb_start((float)e, (float)p.hb_c, (float)p.hb_n);
+        if (!(x > C(1e-30))) {  // below the float range: the bound and start of FP32, in double
+            hi = fmin(hi, d_pow(e / p.hb_c, C(1) / p.hb_n));
+            if (!(hi > C(0))) return C(0);
+            x = fmin(e / (C(0.5) + p.hb_c), hi);
+        } else if (!(x < hi)) {
+            x = C(0.5) * hi;
+        }
+    } else {
+        hi = fmin(C(2) * e, d_pow(e / p.hb_c, C(1) / p.hb_n));
+        if (!(hi > C(0))) return C(0);
+        x = fmin(e / (C(0.5) + p.hb_c), hi);
+    }
     for (int it = 0; it < 64; ++it) {
         const C xn1 = d_pow(x, p.hb_n - C(1));  // s^(n-1); x > 0 here
         const C F = C(0.5) * x + p.hb_c * xn1 * x - e;
@@ -282,7 +324,7 @@ __device__ __forceinline__ C hb_moment(C Tn, const Coll<C>& p)
         else lo = x;
         const C step = F / (C(0.5) + p.hb_c * p.hb_n * xn1);
         C xn = x - step;
-        const bool conv = fabs(step) <= tol * x;
+        const bool conv = fabs(step) <= last * x;
         if (!conv && !(xn > lo && xn < hi)) xn = C(0.5) * (lo + hi);
         const bool done = conv || hi - lo <= tol * hi;
         x = xn;
