@@ -90,8 +90,11 @@ typedef enum { LBM_COMPACT = 0, LBM_DENSE = 1 } lbm_layout;
  * of solid nodes idle; fastest when most nodes are fluid).  SLOTS runs one
  * thread per fluid slot, 64 consecutive slots per wavefront (every lane
  * busy; fastest when most nodes are solid).  AUTO (default) takes SLOTS
- * when fewer than 45% of the nodes are fluid, else ROWS.  Identical
- * results. */
+ * when fewer than 45% of the nodes are fluid, else ROWS; and for a small
+ * domain (AA, no MRT, no FP64 redo, default tile and tile order) the steps
+ * between monitor records are taken several per launch, the populations of a
+ * tile held in the local memory of a compute unit and a second copy of them
+ * in the work buffer's staging area.  Identical results. */
 typedef enum { LBM_PULL_AUTO = 0, LBM_PULL_SLOTS = 1, LBM_PULL_ROWS = 2 } lbm_pull_form;
 
 typedef struct {
@@ -319,8 +322,8 @@ int lbm_get_tile_order(lbm_domain* dom, int32_t* brick_rows, int32_t* brick_plan
 int lbm_set_pull_form(lbm_domain* dom, int32_t form);
 int lbm_get_pull_form(lbm_domain* dom, int32_t* form);
 /* Time candidate tile shapes (compact layout: and both neighbour-phase
- * kernels) on the bound buffers (the state is saved and restored around the
- * trial steps) and keep the fastest; synchronises. */
+ * kernels, and several steps per launch where AUTO takes them) on the bound
+ * buffers (the state is saved and restored around the trial steps) and keep the fastest; synchronises. */
 int lbm_autotune(lbm_domain* dom, int32_t trial_steps);
 
 int lbm_destroy(lbm_domain* dom);

@@ -523,6 +523,16 @@ hipError_t launch_batch_step(int lat, int prec, int pat, bool mon, const BatchAr
     }
 }
 
+hipError_t launch_multi(int lat, int op, int prec, const MultiArgs& a, size_t lds, hipStream_t s, int* max_box)
+{
+    switch (lat) {
+    case 0: return launch_multi_lattice<0>(op, prec, a, lds, s, max_box);
+    case 1: return launch_multi_lattice<1>(op, prec, a, lds, s, max_box);
+    case 2: return launch_multi_lattice<2>(op, prec, a, lds, s, max_box);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 hipError_t launch_batch_finalize(const BatchArgs& a, const int* /*unused*/, void* records, const int64_t* counter,
                                  int64_t step, int capacity, hipStream_t s)
 {

@@ -153,6 +153,14 @@ struct lbm_domain {
     uint64_t gen = 0;        // bumped by every change to what the step launches bake in
     uint64_t graph_gen = 0;  // gen the graph was captured at
     double* scratch = nullptr;  // this GPU's allocation-free monitor scratch (resolved by lbm_bind)
+    // several steps per launch (small AA domains, compact layout)
+    bool tile_set = false;   // tile or order chosen by the caller: keep the per-step kernels
+    size_t lds_bytes = 0;    // LDS a block may use and CUs of the bound GPU
+    int cus = 0;
+    struct {
+        int steps = 0;       // per launch; 0: the per-step kernels are faster
+        int c[3] = {0, 0, 0};  // tile
+    } multi;
 };
 
 namespace {
@@ -414,6 +422,222 @@ int run_steps(lbm_domain* dm, int64_t nsteps, hipStream_t st)
     return LBM_OK;
 }
 
+// ---------------------------------------------------------------------------
+// several steps per launch (k_multi)
+// ---------------------------------------------------------------------------
+
+// LDS bytes k_multi keeps per node of its box: populations, relaxation time,
+// neighbour mask, slot (domains with solids) and fluid flag.
+size_t multi_node_bytes(const lbm_domain* dm)
+{
+    const size_t es = prec_bytes(dm->d.precision);
+    return dm->Q * es + (dm->r.op == LBM_PR ? std::max<size_t>(es, 4) : 0) + 4 + (dm->Nf == dm->N ? 0 : 4) + 1;
+}
+
+// Direction stride of the second population copy, kept in the staging area
+// (nothing else uses it while steps run): slots rounded to 64 if there is
+// room.  0: no room.
+int64_t multi_stride(const lbm_domain* dm)
+{
+    const size_t es = prec_bytes(dm->d.precision);
+    const size_t per = dm->Q * es + (dm->r.op == LBM_PR ? std::max<size_t>(es, 4) : 0);
+    const size_t room = dm->L.work - dm->L.stage;
+    const int64_t up = (dm->Nf + 63) / 64 * 64;
+    return up * per <= room ? up : dm->Nf * per <= room ? dm->Nf : 0;
+}
+
+void multi_box(const lbm_domain* dm, const int (&c)[3], int steps, int (&h)[3], int64_t& nodes, int64_t& tiles)
+{
+    const int n[3] = {dm->d.nx, dm->d.ny, dm->d.nz};
+    nodes = tiles = 1;
+    for (int a = 0; a < 3; ++a) {
+        h[a] = c[a] < n[a] ? steps : 0;
+        nodes *= c[a] + 2 * h[a];
+        tiles *= (n[a] + c[a] - 1) / c[a];
+    }
+}
+
+// Most nodes of a domain that one block may hold whole.
+int multi_box_nodes(const lbm_domain* dm)
+{
+    int n = 0;
+    return launch_multi(dm->d.lattice, dm->r.op, dm->d.precision, MultiArgs{}, 0, nullptr, &n) == hipSuccess ? n : 0;
+}
+
+// Time model behind the choice, microseconds, fitted to 900 runs on D2Q9,
+// D3Q19 and D3Q27 ducts of 48^2 to 200^2 nodes (every precision; IR and PR
+// within 13%).  A launch costs 4.1 to 4.7 plus, for each round of blocks over
+// the CUs (15% more when there are several), 2.8 per 100 KB of populations loaded, a latency per step (the
+// dependent chain of one node update) and the vector work of the fullest
+// SIMD: its waves times `wave`.  PRI and IRHB iterate per node; they are
+// counted three times the work of IR and kept to one round.
+double multi_cost(const lbm_domain* dm, const int (&c)[3], int steps)
+{
+    int h[3];
+    int64_t M, tiles;
+    multi_box(dm, c, steps, h, M, tiles);
+    if ((M + 3) / 4 * 4 * multi_node_bytes(dm) > dm->lds_bytes) return 1e30;
+    const bool solve = dm->r.op == LBM_PRI || dm->r.op == LBM_IRHB;
+    const double work = (solve ? 3.0 : dm->r.op == LBM_PR ? 1.5 : 1.0) * (dm->d.precision == LBM_FP16 ? 1.3 : 1.0);
+    const double wave = (0.15 + 0.015 * dm->Q) * work, lat = 0.25 + 0.036 * dm->Q;
+    const int64_t rounds = (tiles + dm->cus - 1) / dm->cus;
+    if (solve && rounds > 1) return 1e30;
+    double t = 2.8e-5 * (double)M * dm->Q * (double)prec_bytes(dm->d.precision);
+    for (int s = 1; s <= steps; ++s) {
+        int64_t e = 1;
+        for (int a = 0; a < 3; ++a) e *= c[a] + 2 * (h[a] ? h[a] - s : 0);
+        t += lat + wave * (double)((e + 255) / 256);
+    }
+    return ((double)rounds * (rounds > 1 ? 1.15 : 1.0) * t + 3.8 + 0.035 * dm->Q) / steps;
+}
+
+// The per-step kernels on a cache-resident domain (the same runs, and boxes up
+// to 256 x 256 x 4 and 1000^2): launch and latency, then 5 TB/s, 10 TB/s past
+// 30 MB a step.
+double steps_cost(const lbm_domain* dm)
+{
+    const double mb = 2e-6 * (double)dm->Nf * dm->Q * (double)prec_bytes(dm->d.precision);
+    const double solve = dm->r.op == LBM_IR ? 0.0 : dm->r.op == LBM_PR ? 0.4 : 1.5;
+    return 4.2 + 0.02 * dm->Q + 0.2 * std::min(mb, 30.0) + 0.1 * std::max(mb - 30.0, 0.0) + solve;
+}
+
+// Choose tile and steps per launch, or none: k_multi has to promise a fifth
+// less than the per-step kernels.  Tiles cut the axes evenly into parts of
+// about 4 to 32 nodes (or span them); the halo's redundant updates grow with
+// the steps, the launches and loads they share shrink.
+void plan_multi(lbm_domain* dm)
+{
+    dm->multi.steps = 0;
+    if (dm->d.scheme != LBM_AA || dm->d.layout != LBM_COMPACT || dm->Nf < 1 || dm->cus < 1) return;
+    if (kernel_op(dm->r) & OP_MRT) return;
+    if (dm->d.precision != LBM_FP64 && dm->r.fp64_fallback) return;
+    const int n[3] = {dm->d.nx, dm->d.ny, dm->d.nz};
+    double best = 0.8 * steps_cost(dm);
+    if (dm->N <= multi_box_nodes(dm)) {
+        const int c[3] = {n[0], n[1], n[2]};
+        const double us = multi_cost(dm, c, 64);  // no halo: the cost per step falls with the steps
+        if (us < best) {
+            best = us;
+            dm->multi.steps = 4096;
+            std::copy(c, c + 3, dm->multi.c);
+        }
+    }
+    if (multi_stride(dm) == 0) return;
+    std::vector<int> cut[3];
+    for (int a = 0; a < 3; ++a) {
+        if (n[a] <= 64) cut[a].push_back(n[a]);
+        for (int want : {4, 6, 8, 12, 16, 24, 32}) {
+            const int parts = (n[a] + want - 1) / want, c = (n[a] + parts - 1) / parts;
+            if (c < n[a] && (cut[a].empty() || cut[a].back() != c)) cut[a].push_back(c);
+        }
+    }
+    for (int cz : cut[2])
+        for (int cy : cut[1])
+            for (int cx : cut[0]) {
+                const int c[3] = {cx, cy, cz};
+                if (cx == n[0] && cy == n[1] && cz == n[2]) continue;
+                for (int T = 2; T <= 16; T += T < 8 ? 2 : 4) {
+                    const double us = multi_cost(dm, c, T);
+                    if (us >= 1e30) break;  // outgrows the LDS, or never fits
+                    if (us < best) {
+                        best = us;
+                        dm->multi.steps = T;
+                        std::copy(c, c + 3, dm->multi.c);
+                    }
+                }
+            }
+}
+
+int launch_multi_steps(lbm_domain* dm, int steps, bool back, hipStream_t st)
+{
+    const auto& pl = dm->multi;
+    MultiArgs a{};
+    int64_t M, tiles;
+    multi_box(dm, pl.c, steps, a.h, M, tiles);
+    for (int k = 0; k < 3; ++k) {
+        a.c[k] = pl.c[k];
+        a.e[k] = a.c[k] + 2 * a.h[k];
+        a.per[k] = dm->d.periodic[k] ? 1 : 0;
+    }
+    if (dm->D == 2) a.per[2] = 1;
+    a.n[0] = dm->d.nx;
+    a.n[1] = dm->d.ny;
+    a.n[2] = dm->d.nz;
+    char* const second = dm->work + dm->L.stage;
+    const int64_t s2 = multi_stride(dm);
+    char* const tau2 = second + (size_t)dm->Q * s2 * prec_bytes(dm->d.precision);
+    a.src = back ? (const void*)second : dm->pdf;
+    a.s_src = back ? s2 : dm->S;
+    a.tau_src = back ? (const void*)tau2 : dm->tau;
+    const bool to_second = tiles > 1 && !back;
+    a.dst = to_second ? (void*)second : dm->pdf;
+    a.s_dst = to_second ? s2 : dm->S;
+    a.tau_dst = to_second ? (void*)tau2 : dm->tau;
+    a.bits = (const uint64_t*)(dm->mask + dm->L.bits_off);
+    a.wbase = (const uint32_t*)(dm->mask + dm->L.base_off);
+    a.W = dm->L.W;
+    a.all_fluid = dm->Nf == dm->N ? 1 : 0;
+    a.ntx = (a.n[0] + a.c[0] - 1) / a.c[0];
+    a.nty = (a.n[1] + a.c[1] - 1) / a.c[1];
+    a.ntz = (a.n[2] + a.c[2] - 1) / a.c[2];
+    a.ntiles = (int)tiles;
+    a.tiles_per_xcd = (a.ntiles + 7) / 8;
+    a.nbox = (int)M;
+    a.M = (int)((M + 3) / 4 * 4);
+    a.steps = steps;
+    a.h16_scale = std::ldexp(1.0f, -dm->r.fp16_scale_log2);
+    a.h16_inv = std::ldexp(1.0f, dm->r.fp16_scale_log2);
+    a.cd = make_coll<double>(dm->r);
+    a.cf = make_coll<float>(dm->r);
+    const size_t lds = a.M * multi_node_bytes(dm);
+    HIPCHK(launch_multi(dm->d.lattice, dm->r.op, dm->d.precision, a, lds, st));
+    dm->t += steps;
+    return LBM_OK;
+}
+
+// Enqueue nsteps steps: by k_multi where the plan says so (between monitor
+// steps, from the post-collision phase), by the per-step kernels otherwise.
+int advance(lbm_domain* dm, int64_t nsteps, hipStream_t st)
+{
+    const bool on = dm->multi.steps > 0 && !dm->tile_set && dm->pull_form == LBM_PULL_AUTO &&
+                    (dm->mon_k == 0 || dm->mon_k > 4);
+    if (!on) return run_steps(dm, nsteps, st);
+    int rc;
+    while (nsteps > 0) {
+        int64_t n = nsteps;  // steps that end at the next monitor step
+        if (dm->mon_k > 0) n = dm->t % dm->mon_k == 0 ? 0 : std::min<int64_t>(n, dm->mon_k - dm->t % dm->mon_k);
+        n -= n % 2;
+        if (dm->parity != 0 || n < 4) {
+            const int64_t k = std::min<int64_t>(nsteps, dm->parity != 0 ? 1 : 2);
+            if ((rc = run_steps(dm, k, st))) return rc;
+            nsteps -= k;
+            continue;
+        }
+        int64_t done = 0;
+        const int T = dm->multi.steps;
+        int h[3];
+        int64_t M, tiles;
+        multi_box(dm, dm->multi.c, 2, h, M, tiles);
+        if (tiles == 1) {  // in place
+            while (n - done >= 2) {
+                const int k = (int)std::min<int64_t>(n - done, T);
+                if ((rc = launch_multi_steps(dm, k, false, st))) return rc;
+                done += k;
+            }
+        } else {  // there and back between the two copies
+            while (n - done >= 4) {
+                const int k = (int)std::min<int64_t>(n - done, 2 * T);
+                const int k1 = (k / 2 + 1) / 2 * 2;
+                if ((rc = launch_multi_steps(dm, k1, false, st))) return rc;
+                if ((rc = launch_multi_steps(dm, k - k1, true, st))) return rc;
+                done += k;
+            }
+        }
+        nsteps -= done;
+    }
+    return LBM_OK;
+}
+
 // The history restarts: host counters and the device ring counter.
 int reset_history(lbm_domain* dm)
 {
@@ -439,7 +663,7 @@ int build_graph(lbm_domain* dm)
     const int cur = dm->cur, parity = dm->parity;
     const std::vector<int64_t> times = dm->hist_time;
     HIPCHK(hipStreamBeginCapture(dm->cap, hipStreamCaptureModeThreadLocal));
-    const int rc = run_steps(dm, dm->graph_steps, dm->cap);
+    const int rc = advance(dm, dm->graph_steps, dm->cap);
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(dm->cap, &g);
     dm->t = t;
@@ -505,6 +729,7 @@ int upload_mask(lbm_domain* dm, const uint8_t* host_mask)
     HIPCHK(hipMemcpyAsync(dm->mask + dm->L.recs_off, cm.recs.data(), cm.recs.size() * sizeof(SegRec),
                           hipMemcpyHostToDevice, dm->stream));
     HIPCHK(hipStreamSynchronize(dm->stream));
+    plan_multi(dm);
     return LBM_OK;
 }
 
@@ -583,6 +808,11 @@ int lbm_bind(lbm_domain* dm, void* pdf_dev, void* tau_dev, void* mask_dev, void*
     // that lbm_monitors_async looks nothing up when it runs (e.g. under
     // graph capture)
     HIPCHK(scratch_partials(dm->stream, &dm->scratch));
+    int dev = 0, lds = 0;
+    HIPCHK(hipStreamGetDevice(dm->stream, &dev));
+    HIPCHK(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+    HIPCHK(hipDeviceGetAttribute(&dm->cus, hipDeviceAttributeMultiprocessorCount, dev));
+    dm->lds_bytes = (size_t)lds;
     dm->bound = true;
     int rc = upload_mask(dm, nullptr);
     if (rc) return rc;
@@ -682,7 +912,7 @@ int lbm_step(lbm_domain* dm, int64_t nsteps)
         if (!graph_ok) {
             int64_t n = nsteps;
             if (G > 0 && dm->t % G != 0) n = std::min<int64_t>(nsteps, G - dm->t % G);
-            if ((rc = run_steps(dm, n, dm->stream))) return rc;
+            if ((rc = advance(dm, n, dm->stream))) return rc;
             nsteps -= n;
             continue;
         }
@@ -917,6 +1147,7 @@ int lbm_set_tile(lbm_domain* dm, int32_t tx, int32_t ty, int32_t tz)
     dm->tx = tx;
     dm->ty = ty;
     dm->tz = tz;
+    dm->tile_set = true;
     dm->gen++;
     return LBM_OK;
 }
@@ -927,6 +1158,7 @@ int lbm_set_tile_order(lbm_domain* dm, int32_t brick_rows, int32_t brick_planes)
     if (brick_rows < 0 || brick_planes < 0) return fail(LBM_EINVAL, "brick sizes must be >= 0 (0 = default)");
     dm->bry = brick_rows;
     dm->brz = brick_planes;
+    dm->tile_set = true;
     dm->gen++;
     return LBM_OK;
 }
@@ -1004,11 +1236,28 @@ int lbm_autotune(lbm_domain* dm, int32_t trial_steps)
         cand = dm->D == 3 ? cand3 : cand2;
         nc = dm->D == 3 ? (int)(sizeof cand3 / sizeof cand3[0]) : (int)(sizeof cand2 / sizeof cand2[0]);
     }
-    int best = -2;  // -1: the slot kernel (compact layout), c >= 0: row kernel with tile c
+    int best = -2;  // -3: k_multi, -1: the slot kernel (compact layout), c >= 0: row kernel with tile c
     float best_ms = 1e30f;
     const int keep[3] = {dm->tx, dm->ty, dm->tz};
     const int keep_form = dm->pull_form;
-    for (int c = dm->d.layout == LBM_COMPACT ? -1 : 0; c < nc && he == hipSuccess; ++c) {
+    const bool keep_set = dm->tile_set;
+    if (dm->multi.steps > 0 && he == hipSuccess) {
+        // several steps per launch, as the default form takes them; even
+        // counts, as a long run has them
+        const int n = std::max(4, (trial_steps + 3) / 4 * 4);
+        dm->tile_set = false;
+        dm->pull_form = LBM_PULL_AUTO;
+        if (dm->parity != 0) rc = run_steps(dm, 1, dm->stream);
+        float ms = 0;
+        if (rc == LBM_OK && (rc = advance(dm, n, dm->stream)) == LBM_OK &&
+            (he = hipEventRecord(e0, dm->stream)) == hipSuccess && (rc = advance(dm, n, dm->stream)) == LBM_OK &&
+            (he = hipEventRecord(e1, dm->stream)) == hipSuccess && (he = hipEventSynchronize(e1)) == hipSuccess &&
+            (he = hipEventElapsedTime(&ms, e0, e1)) == hipSuccess) {
+            best_ms = ms * (float)trial_steps / (float)n;
+            best = -3;
+        }
+    }
+    for (int c = dm->d.layout == LBM_COMPACT ? -1 : 0; c < nc && he == hipSuccess && rc == LBM_OK; ++c) {
         if (c >= 0) {
             const int tx = cand[c][0], ty = cand[c][1], tz = cand[c][2];
             if (check_tile(dm, tx, ty, tz) != LBM_OK) continue;
@@ -1037,6 +1286,7 @@ int lbm_autotune(lbm_domain* dm, int32_t trial_steps)
     dm->ty = keep[1];
     dm->tz = keep[2];
     dm->pull_form = keep_form;
+    dm->tile_set = keep_set;
     const bool ok = rc == LBM_OK && he == hipSuccess;
     if (ok && best >= 0) {
         dm->tx = cand[best][0];
@@ -1044,6 +1294,10 @@ int lbm_autotune(lbm_domain* dm, int32_t trial_steps)
         dm->tz = cand[best][2];
     }
     if (ok && best >= -1 && dm->d.layout == LBM_COMPACT) dm->pull_form = best < 0 ? LBM_PULL_SLOTS : LBM_PULL_ROWS;
+    if (ok && best == -3) {
+        dm->pull_form = LBM_PULL_AUTO;
+        dm->tile_set = false;
+    }
     dm->gen++;
     const int rc_load = lbm_load(dm, saved.data(), bytes);
     if (he != hipSuccess) return fail(LBM_EHIP, "autotune: %s", hipGetErrorString(he));

@@ -150,12 +150,40 @@ struct BatchArgs {
     int xcd_chunks;        // work-item order (k_batch_step); needs a grid that is a multiple of 8
 };
 
+// Several steps of a small domain per launch (multi_impl.hpp): the domain is
+// cut into tiles of c nodes; a block holds its tile and h halo nodes on every
+// side of each axis (h = 0: the tile spans the axis) in LDS.
+struct MultiArgs {
+    const void* src;       // populations read (AA, post-collision swapped), direction stride s_src
+    void* dst;             // populations written, direction stride s_dst; == src only with one tile
+    const void* tau_src;   // PR relaxation time
+    void* tau_dst;
+    const uint64_t* bits;  // fluid bitmap and word bases, as in StepArgs
+    const uint32_t* wbase;
+    int64_t s_src, s_dst;
+    int W;
+    int all_fluid;         // no solid node: slot = node index
+    int n[3], per[3];
+    int c[3], h[3], e[3];  // tile, halo, box (c + 2 h)
+    int ntx, nty, ntz, ntiles, tiles_per_xcd;
+    int nbox;              // nodes of the box
+    int M;                 // nbox rounded up to a multiple of 4: stride of the LDS arrays
+    int steps;             // even
+    float h16_scale, h16_inv;
+    Coll<double> cd;
+    Coll<float> cf;
+};
+
 hipError_t launch_step(int lat, int op, int prec, int pat, bool mon, int layout, const StepArgs& a, hipStream_t s);
 template <int LAT, int PREC>
 hipError_t launch_step_prec(int op, int pat, bool mon, int layout, const StepArgs& a, hipStream_t s);
 template <int LAT>
 hipError_t launch_batch_lattice(int prec, int pat, bool mon, const BatchArgs& a, int grid, hipStream_t s);
 hipError_t launch_batch_step(int lat, int prec, int pat, bool mon, const BatchArgs& a, int grid, hipStream_t s);
+template <int LAT>
+hipError_t launch_multi_lattice(int op, int prec, const MultiArgs& a, size_t lds, hipStream_t s, int* max_box);
+// max_box non-NULL: report the most nodes of a whole-domain box, launch nothing
+hipError_t launch_multi(int lat, int op, int prec, const MultiArgs& a, size_t lds, hipStream_t s, int* max_box = nullptr);
 hipError_t launch_batch_finalize(const BatchArgs& a, const int* sims_item0, void* records, const int64_t* counter,
                                  int64_t step, int capacity, hipStream_t s);
 hipError_t launch_batch_tick(int64_t* counter, hipStream_t s);
