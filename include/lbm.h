@@ -335,7 +335,7 @@ int lbm_destroy(lbm_domain* dom);
  * non-periodic axes) and has its own sizes, operator and rheology; all
  * share one lattice, one precision, the AA scheme, the FP64-fallback flag
  * and the FP16 scale; each holds fewer than 2^31 / Q nodes and uses LBM_PR
- * or LBM_IR.  One step is one persistent kernel launch over a work
+ * or LBM_IR.  One step is one kernel launch over a work
  * list of 256-node items of all simulations (runs of consecutive nodes,
  * or 3-D tiles, per lbm_batch_set_schedule); lbm_batch_step replays a
  * captured hipGraph of graph_steps such launches when it can.  The update
@@ -379,9 +379,9 @@ int lbm_batch_get_tiles(lbm_batch* b, int32_t* tiles);
 /* Scheduling in use: tile policy (0 fewest padded nodes, 1 rows at least
  * 64 wide, 2 fixed 64x4x1, 3, the default, runs of 256 consecutive nodes in
  * node order, rows wrapping, reported by lbm_batch_get_tiles as 256x1x1) and
- * work-item order (0, the default, plain grid stride over the list; 1 one
- * contiguous chunk of the list per XCD so that neighbouring tiles share an
- * L2). */
+ * work-item order (0, the default, plain order of the list, or chunks as in
+ * 1 for an arena that the caches hold; 1 one contiguous chunk of the list per
+ * XCD so that neighbouring tiles share an L2). */
 int lbm_batch_get_schedule(lbm_batch* b, int32_t* tile_policy, int32_t* xcd_order);
 /* Choose the scheduling by hand (the state is kept; results do not depend on
  * it).  LBM_EINVAL outside the ranges above.  Synchronises. */

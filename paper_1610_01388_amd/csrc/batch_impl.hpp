@@ -2,14 +2,15 @@
 // (walls only through non-periodic axes) advanced by one launch per time
 // step.  Every simulation is cut into tiles of 256 nodes; a work item is one
 // tile (in the AA local phase, 256 consecutive nodes), so items are equally
-// sized whatever the simulation's size.  A
-// persistent grid walks the work list; each item reads its simulation's
-// sizes, tile shape, operator and parameters from a device table (wave-
-// uniform, scalar loads), so mixed operators branch per item, not per lane.
+// sized whatever the simulation's size.  One
+// block takes one item and reads its simulation's sizes, tile shape, operator
+// and parameters from a device table (wave-uniform, scalar loads), so mixed
+// operators branch per item, not per lane.
 // The node update is the same collision code as the single-domain kernels,
 // so a simulation gives bitwise the same state batched or alone.
 #pragma once
 
+#include <algorithm>
 #include <type_traits>
 
 #include "step_impl.hpp"
@@ -120,9 +121,14 @@ __device__ __forceinline__ void batch_tile(const BatchArgs& a, const BatchSim& s
 // AA local phase of one item.  This half of the AA pair touches only the
 // node's own slots, so an item names 256 consecutive nodes instead of a tile
 // (a simulation has at least ceil(N / 256) items; the surplus ones are
-// empty) and each direction is one contiguous run per wavefront.  Ordinary
-// loads and stores: with non-temporal hints this phase measured slower.
-template <int LAT, int OP, int PREC, bool MON>
+// empty) and each direction is one contiguous run per wavefront.  NT:
+// non-temporal loads and stores, for arenas larger than the caches: on the
+// 256-duct FP32 sweep 272 us for 319 (6.2 TB/s), and the pull phase, whose
+// lines stay in the caches then, 321 for 342.  (The pull itself keeps ordinary
+// accesses: with non-temporal loads, stores or both it took 376, 330, 456.)
+// Cache-resident sweeps would lose their hits: 12 small ducts 19.1 us a pair
+// for 18.7.
+template <int LAT, int OP, int PREC, bool MON, bool NT>
 __device__ __forceinline__ void batch_local(const BatchArgs& a, const BatchSim& sm, int item)
 {
     using L = Lattice<LAT>;
@@ -146,7 +152,10 @@ __device__ __forceinline__ void batch_local(const BatchArgs& a, const BatchSim& 
         const S* A = (const S*)a.pdf + sm.off_pdf;
         C h[Q];
 #pragma unroll
-        for (int i = 0; i < Q; ++i) h[i] = decode<PREC>(A[i * St + n], L::w[i], a.h16_scale);
+        for (int i = 0; i < Q; ++i) {
+            const S* p = A + (i * St + n);
+            h[i] = decode<PREC>(NT ? ld_stream(p) : *p, L::w[i], a.h16_scale);
+        }
         T* tau = (T*)a.tau + sm.off_tau;
         C tau_prev = C(0);
         if constexpr (has_tau(OP)) tau_prev = (C)tau[n];
@@ -155,7 +164,12 @@ __device__ __forceinline__ void batch_local(const BatchArgs& a, const BatchSim& 
 
         S* B = (S*)a.pdf + sm.off_pdf;
 #pragma unroll
-        for (int i = 0; i < Q; ++i) B[opp(i) * St + n] = encode<PREC>(h[i], L::w[i], a.h16_inv);
+        for (int i = 0; i < Q; ++i) {
+            S* p = B + (opp(i) * St + n);
+            const S v = encode<PREC>(h[i], L::w[i], a.h16_inv);
+            if constexpr (NT) st_stream(v, p);
+            else *p = v;
+        }
         if constexpr (has_tau(OP)) tau[n] = (T)pr.tau_p;
     }
     if constexpr (MON)
@@ -163,59 +177,66 @@ __device__ __forceinline__ void batch_local(const BatchArgs& a, const BatchSim& 
                          a.uprev ? a.uprev + sm.off_u : nullptr, n, St);
 }
 
-// Work-item order.  xcd_chunks == 0: block b takes items b, b + G, ...
-// (G = grid size).  xcd_chunks == 1 (G a multiple of 8): the items are cut
-// into 8 contiguous chunks and the blocks b with b mod 8 == j, which the
-// hardware places on one XCD, walk chunk j; neighbouring tiles of a
-// simulation then share that XCD's L2.  Both orders visit every item once.
+// One block per work item.  xcd_chunks == 0: block b takes item b.
+// xcd_chunks == 1 (8 ceil(nitems / 8) blocks): the items are cut into 8
+// contiguous chunks and the blocks b with b mod 8 == j, which the hardware
+// places on one XCD, take chunk j; neighbouring tiles of a simulation then
+// share that XCD's L2.  Both orders visit every item once.  (4096 persistent
+// blocks looping over the items measured 8% slower on the 256-duct FP32
+// sweep, 362 us a step for 334: the loop waits for the next item's table
+// entries where a fresh block's wait is hidden by its neighbours.)
 // FB: the FP64 redo of near-yield nodes compiled in (reduced precision with
 // the fallback on); without it the kernel holds no FP64 registers.
-template <int LAT, int PREC, int PAT, bool MON, bool FB>
+template <int LAT, int PREC, int PAT, bool MON, bool FB, bool NT>
 __global__ __launch_bounds__(kMaxBlockThreads) void k_batch_step(const BatchArgs a)
 {
     constexpr int F = FB ? OP_FB : 0;
-    int hi = a.nitems, first = blockIdx.x, stride = gridDim.x;
+    const unsigned b = blockIdx.y * gridDim.x + blockIdx.x;
+    unsigned item = b;
     if (a.xcd_chunks) {
-        const int chunk = (a.nitems + 7) >> 3;
-        const int lo = (blockIdx.x & 7) * chunk;
-        hi = min(a.nitems, lo + chunk);
-        first = lo + (blockIdx.x >> 3);
-        stride = gridDim.x >> 3;
+        const unsigned chunk = ((unsigned)a.nitems + 7) >> 3;
+        if ((b >> 3) >= chunk) return;
+        item = (b & 7) * chunk + (b >> 3);
     }
-    for (int item = first; item < hi; item += stride) {
-        const int sim = __builtin_amdgcn_readfirstlane(a.work[item]);
-        const BatchSim& sm = a.sims[sim];
-        // PR or IR (the host rejects PRI for batches: its Newton solve would
-        // raise the register count of this shared kernel for every item)
-        if constexpr (PAT == PAT_AA_LOCAL) {
-            if (sm.op == OP_PR) batch_local<LAT, OP_PR | F, PREC, MON>(a, sm, item);
-            else batch_local<LAT, OP_IR | F, PREC, MON>(a, sm, item);
-        } else {
-            if (sm.op == OP_PR) batch_tile<LAT, OP_PR | F, PREC, PAT, MON>(a, sm, item);
-            else batch_tile<LAT, OP_IR | F, PREC, PAT, MON>(a, sm, item);
-        }
-        // the block reduction's LDS slots are read by thread 0 after its
-        // barrier; the next item must not overwrite them before that
-        if constexpr (MON) __syncthreads();
+    if (item >= (unsigned)a.nitems) return;  // whole block leaves together
+    const int sim = __builtin_amdgcn_readfirstlane(a.work[item]);
+    const BatchSim& sm = a.sims[sim];
+    // PR or IR (the host rejects PRI for batches: its Newton solve would
+    // raise the register count of this shared kernel for every item)
+    if constexpr (PAT == PAT_AA_LOCAL) {
+        if (sm.op == OP_PR) batch_local<LAT, OP_PR | F, PREC, MON, NT>(a, sm, item);
+        else batch_local<LAT, OP_IR | F, PREC, MON, NT>(a, sm, item);
+    } else {
+        if (sm.op == OP_PR) batch_tile<LAT, OP_PR | F, PREC, PAT, MON>(a, sm, item);
+        else batch_tile<LAT, OP_IR | F, PREC, PAT, MON>(a, sm, item);
     }
 }
 
 template <int LAT>
 hipError_t launch_batch_lattice(int prec, int pat, bool mon, const BatchArgs& a, int grid, hipStream_t s)
 {
-    auto go = [&](auto P, auto PT, auto M) {
+    // rows of 2^23 blocks: a grid axis holds fewer than 2^32 threads
+    const dim3 blocks((unsigned)std::min(grid, 1 << 23), (unsigned)((grid + (int64_t)(1 << 23) - 1) >> 23));
+    using std::integral_constant;
+    auto go = [&](auto P, auto PT, auto M, auto NT) {
         constexpr int PV = decltype(P)::value;
+        constexpr int PTV = decltype(PT)::value;
+        constexpr bool MV = decltype(M)::value, NV = decltype(NT)::value;
         if (PV != PREC_F64 && a.fallback)
-            hipLaunchKernelGGL((k_batch_step<LAT, PV, decltype(PT)::value, decltype(M)::value, PV != PREC_F64>),
-                               dim3(grid), dim3(256), 0, s, a);
+            hipLaunchKernelGGL((k_batch_step<LAT, PV, PTV, MV, PV != PREC_F64, NV>), blocks, dim3(256), 0, s, a);
         else
-            hipLaunchKernelGGL((k_batch_step<LAT, PV, decltype(PT)::value, decltype(M)::value, false>), dim3(grid),
-                               dim3(256), 0, s, a);
+            hipLaunchKernelGGL((k_batch_step<LAT, PV, PTV, MV, false, NV>), blocks, dim3(256), 0, s, a);
         return hipGetLastError();
     };
-    using std::integral_constant;
+    // the hint exists for the local phase only
+    auto by_hint = [&](auto P, auto PT, auto M) {
+        if constexpr (decltype(PT)::value == PAT_AA_LOCAL) {
+            if (a.stream_hint) return go(P, PT, M, integral_constant<bool, true>{});
+        }
+        return go(P, PT, M, integral_constant<bool, false>{});
+    };
     auto by_mon = [&](auto P, auto PT) {
-        return mon ? go(P, PT, integral_constant<bool, true>{}) : go(P, PT, integral_constant<bool, false>{});
+        return mon ? by_hint(P, PT, integral_constant<bool, true>{}) : by_hint(P, PT, integral_constant<bool, false>{});
     };
     auto by_pat = [&](auto P) {
         switch (pat) {

@@ -117,8 +117,7 @@ struct NodeArgs {
 
 // Batched sweep: many independent all-fluid domains (walls only through
 // non-periodic axes) stepped together.  Each simulation is cut into work
-// items of 256 nodes (runs of consecutive nodes, or 3-D tiles); a persistent
-// grid walks the work list.
+// items of 256 nodes (runs of consecutive nodes, or 3-D tiles), one block each.
 struct BatchSim {
     int nx, ny, nz;
     int per[3];
@@ -147,6 +146,7 @@ struct BatchArgs {
     double* uprev;         // MON: previous-velocity blocks (BatchSim::off_u)
     float h16_scale, h16_inv;
     int fallback;
+    int stream_hint;       // non-temporal access in the local phase (arena larger than the caches)
     int xcd_chunks;        // work-item order (k_batch_step); needs a grid that is a multiple of 8
 };
 
