@@ -395,10 +395,12 @@ int run_steps(lbm_domain* dm, int64_t nsteps, hipStream_t st)
             pat = PAT_AB;
             a.src = copy_ptr(dm, dm->cur);
             a.dst = copy_ptr(dm, 1 - dm->cur);
+            a.rev = dm->d.layout == LBM_COMPACT ? (int)(dm->t & 1) : 0;
         } else {
             pat = dm->parity == 0 ? PAT_AA_PULL : PAT_AA_LOCAL;
             a.src = dm->pdf;
             a.dst = dm->pdf;
+            a.rev = dm->d.layout == LBM_COMPACT ? dm->parity : 0;
         }
         const bool mon = dm->mon_k > 0 && (dm->t % dm->mon_k) == 0;
         HIPCHK(launch_step(dm->d.lattice, kernel_op(dm->r) | (a.fallback ? OP_FB : 0), dm->d.precision, pat, mon,
@@ -470,7 +472,7 @@ int multi_box_nodes(const lbm_domain* dm)
 // the CUs (15% more when there are several), 2.8 per 100 KB of populations loaded, a latency per step (the
 // dependent chain of one node update) and the vector work of the fullest
 // SIMD: its waves times `wave`.  PRI and IRHB iterate per node; they are
-// counted three times the work of IR and kept to one round.
+// counted four and three times the work of IR and kept to one round.
 double multi_cost(const lbm_domain* dm, const int (&c)[3], int steps)
 {
     int h[3];
@@ -478,7 +480,7 @@ double multi_cost(const lbm_domain* dm, const int (&c)[3], int steps)
     multi_box(dm, c, steps, h, M, tiles);
     if ((M + 3) / 4 * 4 * multi_node_bytes(dm) > dm->lds_bytes) return 1e30;
     const bool solve = dm->r.op == LBM_PRI || dm->r.op == LBM_IRHB;
-    const double work = (solve ? 3.0 : dm->r.op == LBM_PR ? 1.5 : 1.0) * (dm->d.precision == LBM_FP16 ? 1.3 : 1.0);
+    const double work = (dm->r.op == LBM_PRI ? 4.0 : solve ? 3.0 : dm->r.op == LBM_PR ? 1.5 : 1.0) * (dm->d.precision == LBM_FP16 ? 1.3 : 1.0);
     const double wave = (0.15 + 0.015 * dm->Q) * work, lat = 0.25 + 0.036 * dm->Q;
     const int64_t rounds = (tiles + dm->cus - 1) / dm->cus;
     if (solve && rounds > 1) return 1e30;

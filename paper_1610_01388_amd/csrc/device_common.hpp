@@ -46,6 +46,15 @@ __device__ __forceinline__ void st_stream(S v, S* p)
     __builtin_nontemporal_store(v, p);
 }
 
+// The XCDs take consecutive workgroups in turn: workgroup b gets place b / 8 of
+// the (b mod 8)-th of 8 contiguous ranges of `per` tiles, walked from its end
+// with rev set.
+__device__ __forceinline__ int64_t xcd_place(unsigned b, int per, int rev)
+{
+    const int q = (int)(b >> 3);
+    return (int64_t)(b & 7) * per + (rev ? per - 1 - q : q);
+}
+
 // Wrap a halo coordinate g in [-1, n]: periodic axes wrap, walls give
 // "outside" (treated as solid: halfway bounce-back at the face).
 __device__ __forceinline__ int wrap_halo(int g, int n, int per, bool& out)

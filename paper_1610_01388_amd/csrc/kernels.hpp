@@ -82,6 +82,7 @@ struct StepArgs {
     int ntiles;
     int tiles_per_xcd;     // ceil(ntiles / 8): tiles handed to each XCD as one contiguous range
     int bry, brz;          // tile order: bricks of whole rows x bry row-blocks x brz planes
+    int rev;               // walk the tiles (slot blocks) backwards
     int stream_hint;       // non-temporal access where the kernel supports it (state larger than the caches)
     int fallback;          // reduced precision: FP64 redo of near-yield nodes
     float h16_scale;       // FP16: 2^-k  (h = half * w * 2^-k)

@@ -119,8 +119,7 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_step(const StepArgs a)
     constexpr bool PULLS = (PAT != PAT_AA_LOCAL);
     extern __shared__ uint8_t halo[];
 
-    const int b = blockIdx.x;
-    const int tile = (b & 7) * a.tiles_per_xcd + (b >> 3);
+    const int tile = (int)xcd_place(blockIdx.x, a.tiles_per_xcd, a.rev);
     if (tile >= a.ntiles) return;  // whole block leaves together
 
     const int t = threadIdx.x;
@@ -250,8 +249,7 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_step_compact(const StepArg
     // but which measured faster for FP64 IR and plain reduced precision.
     constexpr bool SEL = (PREC == PREC_F64 && op_base(OP) != OP_IR) || (OP & OP_FB) != 0;
 
-    const int b = blockIdx.x;
-    const int tile = (b & 7) * a.tiles_per_xcd + (b >> 3);
+    const int tile = (int)xcd_place(blockIdx.x, a.tiles_per_xcd, a.rev);
     if (tile >= a.ntiles) return;  // whole block leaves together
 
     const int lane = threadIdx.x & 63;
@@ -478,8 +476,7 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_step_rows(const StepArgs a
     // registers to spare) or rebuild them after the collision (FP64)
     constexpr bool KEEP = sizeof(S) < 8;
 
-    const int b = blockIdx.x;
-    const int tile = (b & 7) * a.tiles_per_xcd + (b >> 3);
+    const int tile = (int)xcd_place(blockIdx.x, a.tiles_per_xcd, a.rev);
     if (tile >= a.ntiles) return;  // whole block leaves together
 
     const int lane = threadIdx.x & 63;
@@ -596,8 +593,13 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_step_rows(const StepArgs a
 // geometry at all.  One thread per fluid slot, 256 slots per block: every
 // lane is busy and each direction is one contiguous run per wavefront.
 // NT: non-temporal loads and stores, for states larger than the caches
-// (a cache-resident state would only lose its hits).  Monitor partials: one
-// per block.
+// (a cache-resident state would only lose its hits).  Those walk the slots in
+// one sequence from the end, which the pull left last (eight sequences, one
+// per XCD, cost 4% in FP64 and 7% in FP16); smaller states take the pull's
+// eight ranges, each XCD its own, backwards: what the pull touched last is
+// still cached (a 382 MB tight medium 715 -> 690 us for 4 steps; A/B alternates
+// the direction in the same way, 2 x 179 MB plates 835 -> 771 for 10).
+// Monitor partials: one per block.
 template <int LAT, int OP, int PREC, bool MON, bool NT>
 __global__ __launch_bounds__(kMaxBlockThreads) void k_local_slots(const StepArgs a)
 {
@@ -607,7 +609,10 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_local_slots(const StepArgs
     using C = typename Store<PREC>::C;
     using T = typename Store<PREC>::T;
 
-    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t nblk = (a.nfluid + 255) >> 8;
+    const int64_t cb = NT ? nblk - 1 - blockIdx.x : xcd_place(blockIdx.x, a.slot_bpx, a.rev);
+    if (cb < 0 || cb >= nblk) return;  // whole block leaves together
+    const int64_t k = cb * 256 + threadIdx.x;
     const bool active = k < a.nfluid;
     const int64_t St = a.S;
     const Coll<C>& cp = coll_of<C>(a);
@@ -638,7 +643,7 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_local_slots(const StepArgs
         if constexpr (has_tau(OP)) ((T*)a.tau)[k] = (T)pr.tau_p;
     }
     if constexpr (MON)
-        monitor_block<C>(active, mo, pr, cp, used_fb, a.partials + (int64_t)blockIdx.x * MP_COUNT, a.uprev, k, St);
+        monitor_block<C>(active, mo, pr, cp, used_fb, a.partials + cb * MP_COUNT, a.uprev, k, St);
 }
 
 // Position of the set bit of v with r set bits below it (r < popcount(v)).
@@ -681,8 +686,7 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_pull_slots(const StepArgs 
     static_assert(PAT == PAT_AB || PAT == PAT_AA_PULL, "neighbour phases only");
 
     const int64_t nblk = (a.nfluid + 255) >> 8;
-    const int b = blockIdx.x;
-    const int64_t cb = (int64_t)(b & 7) * a.slot_bpx + (b >> 3);
+    const int64_t cb = xcd_place(blockIdx.x, a.slot_bpx, a.rev);
     if (cb >= nblk) return;  // whole block leaves together
     const int64_t k = cb * 256 + threadIdx.x;
     const bool active = k < a.nfluid;
@@ -818,7 +822,7 @@ static hipError_t go_step(int layout, const StepArgs& a, hipStream_t s)
     const int threads = a.tx * a.ty * a.tz;
     const dim3 grid(8 * a.tiles_per_xcd);
     if (layout == LAYOUT_COMPACT && PAT == PAT_AA_LOCAL) {
-        const int64_t blocks = (a.nfluid + 255) / 256;
+        const int blocks = 8 * a.slot_bpx;
         if (blocks > 0) {
             if (a.stream_hint)
                 hipLaunchKernelGGL((k_local_slots<LAT, OP, PREC, MON, true>), dim3((unsigned)blocks), dim3(256), 0, s, a);
