@@ -310,6 +310,15 @@ void tile_order(const lbm_domain* dm, int ntx, int nty, int ntz, int& bry, int& 
     brz = std::max(1, std::min(brz, ntz));
 }
 
+Divider make_divider(int64_t d)
+{
+    Divider v{};
+    v.d = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(d, INT32_MAX));
+    while ((1ull << v.s) < v.d) ++v.s;
+    v.m = (uint32_t)(((1ull << 32) * ((1ull << v.s) - v.d)) / v.d + 1);
+    return v;
+}
+
 StepArgs step_args(lbm_domain* dm)
 {
     StepArgs a{};
@@ -344,6 +353,17 @@ StepArgs step_args(lbm_domain* dm)
     a.ntiles = a.ntx * a.nty * a.ntz;
     a.tiles_per_xcd = (a.ntiles + 7) / 8;
     tile_order(dm, a.ntx, a.nty, a.ntz, a.bry, a.brz);
+    {
+        const int64_t last_z = a.ntz - (int64_t)((a.ntz - 1) / a.brz) * a.brz;  // planes of the last slab
+        const int64_t last_y = a.nty - (int64_t)((a.nty - 1) / a.bry) * a.bry;  // tile rows of the last brick
+        a.dv_ntx = make_divider(a.ntx);
+        a.dv_zb = make_divider((int64_t)a.ntx * a.nty * a.brz);
+        a.dv_yb[0] = make_divider((int64_t)a.ntx * a.bry * a.brz);
+        a.dv_yb[1] = make_divider((int64_t)a.ntx * a.bry * last_z);
+        a.dv_by[0] = make_divider(a.bry);
+        a.dv_by[1] = make_divider(last_y);
+        a.ty_inv = 65536u / (uint32_t)a.ty + 1u;
+    }
     // non-temporal hints when the population state exceeds 512 MiB, twice
     // the 256 MB last-level cache: a state that still partly fits keeps its
     // cache hits
@@ -400,7 +420,9 @@ int run_steps(lbm_domain* dm, int64_t nsteps, hipStream_t st)
             pat = dm->parity == 0 ? PAT_AA_PULL : PAT_AA_LOCAL;
             a.src = dm->pdf;
             a.dst = dm->pdf;
-            a.rev = dm->d.layout == LBM_COMPACT ? dm->parity : 0;
+            // the local phase walks backwards (see k_local_slots)
+            const double bytes = (double)dm->Q * (double)dm->S * (double)prec_bytes(dm->d.precision);
+            a.rev = dm->parity != 0 && dm->d.layout == LBM_COMPACT && (bytes <= 400e6 || bytes > 1e9) ? 1 : 0;
         }
         const bool mon = dm->mon_k > 0 && (dm->t % dm->mon_k) == 0;
         HIPCHK(launch_step(dm->d.lattice, kernel_op(dm->r) | (a.fallback ? OP_FB : 0), dm->d.precision, pat, mon,

@@ -139,6 +139,8 @@ bool build_compact_mask(int nx, int ny, int nz, const int per[3], const uint8_t*
                 else s.lidx = per[0] ? slot(r, nx - 1) : kNoSlot;
                 if (xl + 1 < nx) s.ridx = slot(r, xl + 1);
                 else s.ridx = per[0] ? slot(r, 0) : kNoSlot;
+                s.lbit = s.lidx != kNoSlot ? 1u : 0u;
+                s.rword = s.ridx != kNoSlot ? 1ull << (xl - x0) : 0ull;
             }
         }
     }

@@ -55,6 +55,13 @@ __host__ __device__ constexpr bool mp_is_max(int k) { return k == MP_UMAX || k =
 //                  (SegRec), read by the row-segment kernel.
 enum { LAYOUT_COMPACT = 0, LAYOUT_DENSE = 1 };  // same values as lbm_layout
 
+// Division by a launch constant d >= 1 of t < 2^31: (mulhi(t, m) + t) >> s with
+// s = ceil(log2 d), m = floor(2^32 (2^s - d) / d) + 1 (Granlund and Montgomery,
+// "Division by invariant integers using multiplication", PLDI 1994).
+struct Divider {
+    uint32_t d, m, s;
+};
+
 struct StepArgs {
     const void* src;       // populations read
     void* dst;             // populations written (== src for AA)
@@ -81,6 +88,8 @@ struct StepArgs {
     int ntx, nty, ntz;     // tiles per axis
     int ntiles;
     int tiles_per_xcd;     // ceil(ntiles / 8): tiles handed to each XCD as one contiguous range
+    Divider dv_ntx, dv_zb, dv_yb[2], dv_by[2];  // tile_coords; [1]: in the last, shorter slab / brick
+    uint32_t ty_inv;       // floor(2^16 / ty) + 1: (n ty_inv) >> 16 = n / ty for n < 4
     int bry, brz;          // tile order: bricks of whole rows x bry row-blocks x brz planes
     int rev;               // walk the tiles (slot blocks) backwards
     int stream_hint;       // non-temporal access where the kernel supports it (state larger than the caches)

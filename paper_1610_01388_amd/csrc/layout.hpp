@@ -22,7 +22,11 @@ constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
 //         or nx - 1 across a periodic x boundary), kNoSlot if it is solid or
 //         beyond a wall;
 //   ridx: the same for the right neighbour of the segment's last node
-//         (min(64 w + 63, nx - 1) + 1, or node 0 across a periodic boundary).
+//         (min(64 w + 63, nx - 1) + 1, or node 0 across a periodic boundary);
+//   lbit, rword: what the bits shifted by one node lack at the segment's ends:
+//         (bits << 1) | lbit and (bits >> 1) | rword are the fluid bits of the
+//         x - 1 and x + 1 neighbours (lbit: left neighbour fluid; rword: the
+//         last node's bit, set when the right neighbour is fluid).
 // The table has (ny + 2) (nz + 2) rows of W records: rows y = -1, ny and
 // z = -1, nz are halo rows, copies of the wrapped rows on periodic axes and
 // empty (every node solid) behind walls, so that the 9 (3-D) or 3 (2-D) rows
@@ -33,8 +37,8 @@ struct SegRec {
     uint32_t base;
     uint32_t lidx;
     uint32_t ridx;
-    uint32_t pad0;
-    uint64_t pad1;
+    uint32_t lbit;
+    uint64_t rword;
 };
 static_assert(sizeof(SegRec) == 32, "segment records are 32 bytes");
 

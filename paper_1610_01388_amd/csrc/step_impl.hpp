@@ -54,7 +54,34 @@ __device__ __forceinline__ void collide_node(typename Store<PREC>::C (&h)[Lattic
 // also streams) is still in the L2 the second time.  With one z-slab per
 // XCD-contiguous range of tiles, the slab's neighbours stay on one XCD.  A
 // bijection of [0, ntiles) for any bry in [1, nty], brz in [1, ntz].
+__device__ __forceinline__ int divide(int t, const Divider& v)
+{
+    return (int)((__umulhi((uint32_t)t, v.m) + (uint32_t)t) >> v.s);
+}
+
+// by value: a reference chosen at run time would move the arguments to memory
+__device__ __forceinline__ Divider pick(bool c, Divider x, Divider y)
+{
+    return Divider{c ? x.d : y.d, c ? x.m : y.m, c ? x.s : y.s};
+}
+
 __device__ __forceinline__ void tile_coords(const StepArgs& a, int t, int& ttx, int& tty, int& ttz)
+{
+    const int zb = divide(t, a.dv_zb);
+    const int u = t - zb * (int)a.dv_zb.d;
+    const Divider dy = pick((zb + 1) * a.brz > a.ntz, a.dv_yb[1], a.dv_yb[0]);
+    const int yb = divide(u, dy);
+    const int v = u - yb * (int)dy.d;
+    const int r = divide(v, a.dv_ntx);
+    ttx = v - r * (int)a.dv_ntx.d;
+    const Divider db = pick((yb + 1) * a.bry > a.nty, a.dv_by[1], a.dv_by[0]);
+    const int q = divide(r, db);
+    tty = yb * a.bry + (r - q * (int)db.d);
+    ttz = zb * a.brz + q;
+}
+
+// The same by plain divisions (row kernel of streamed reduced-precision states).
+__device__ __forceinline__ void tile_coords_slow(const StepArgs& a, int t, int& ttx, int& tty, int& ttz)
 {
     const int per_zb = a.ntx * a.nty * a.brz;
     const int zb = t / per_zb;
@@ -414,38 +441,53 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v)
     return ((uint64_t)hi << 32) | lo;
 }
 
-// Raw buffer access to population storage: a 32-bit byte offset from the
-// descriptor's base, range-checked against its size (accesses past it read
-// zero and write nothing).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t pop_rsrc(const void* base, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
-}
-template <class S> __device__ __forceinline__ S buf_ld(__amdgpu_buffer_rsrc_t r, uint32_t off);
-template <> __device__ __forceinline__ double buf_ld<double>(__amdgpu_buffer_rsrc_t r, uint32_t off)
-{
-    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
-}
-template <> __device__ __forceinline__ float buf_ld<float>(__amdgpu_buffer_rsrc_t r, uint32_t off)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
-}
-template <> __device__ __forceinline__ _Float16 buf_ld<_Float16>(__amdgpu_buffer_rsrc_t r, uint32_t off)
-{
-    return __builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0));
-}
+// Raw buffer access to population storage by element index e from the
+// descriptor's base, range-checked against its elements (accesses past them
+// read zero and write nothing).  (Scaling by the hardware, from an indexed
+// descriptor, measured the same for FP16 and 1.5% slower for FP32.)
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void buf_st(double v, __amdgpu_buffer_rsrc_t r, uint32_t off)
+template <class S>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t pop_rsrc(const S* base, uint32_t elements)
 {
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), r, off, 0, 0);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<S*>(base), 0, (int)(elements * (uint32_t)sizeof(S)), 0x00020000);
 }
-__device__ __forceinline__ void buf_st(float v, __amdgpu_buffer_rsrc_t r, uint32_t off)
+template <class S> __device__ __forceinline__ S buf_ld(__amdgpu_buffer_rsrc_t r, uint32_t e);
+template <> __device__ __forceinline__ double buf_ld<double>(__amdgpu_buffer_rsrc_t r, uint32_t e)
 {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, 0, 0);
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, e << 3, 0, 0));
 }
-__device__ __forceinline__ void buf_st(_Float16 v, __amdgpu_buffer_rsrc_t r, uint32_t off)
+template <> __device__ __forceinline__ float buf_ld<float>(__amdgpu_buffer_rsrc_t r, uint32_t e)
 {
-    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, off, 0, 0);
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, e << 2, 0, 0));
+}
+template <> __device__ __forceinline__ _Float16 buf_ld<_Float16>(__amdgpu_buffer_rsrc_t r, uint32_t e)
+{
+    return __builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r, e << 1, 0, 0));
+}
+__device__ __forceinline__ void buf_st(double v, __amdgpu_buffer_rsrc_t r, uint32_t e)
+{
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), r, e << 3, 0, 0);
+}
+__device__ __forceinline__ void buf_st(float v, __amdgpu_buffer_rsrc_t r, uint32_t e)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, e << 2, 0, 0);
+}
+__device__ __forceinline__ void buf_st(_Float16 v, __amdgpu_buffer_rsrc_t r, uint32_t e)
+{
+    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, e << 1, 0, 0);
+}
+
+// old with the wave-uniform v in the given lane
+__device__ uint32_t write_lane(uint32_t v, uint32_t lane, uint32_t old) __asm("llvm.amdgcn.writelane.i32");
+
+// a + b + (bit `lane` of mask): one v_addc_co_u32 that takes the lane mask as
+// its carry.
+__device__ __forceinline__ uint32_t add_bit(uint32_t a, uint32_t b, uint64_t mask)
+{
+    uint32_t r;
+    uint64_t carry;
+    asm("v_addc_co_u32 %0, %1, %2, %3, %4" : "=v"(r), "=s"(carry) : "v"(a), "v"(b), "s"(mask));
+    return r;
 }
 
 // Compact layout, neighbour phases (AA pull, A/B), row-segment waves with
@@ -456,12 +498,24 @@ __device__ __forceinline__ void buf_st(_Float16 v, __amdgpu_buffer_rsrc_t r, uin
 // descriptor of its direction pair {i, opp(i)} (the two arrays a lane
 // chooses between: the neighbour's slot in one, its own slot in the other),
 // at a 32-bit element offset picked per lane by the fluid mask of the
-// neighbour -- a select and an add per access, no branch and no 64-bit
-// address arithmetic.  In the AA pull the store of direction i goes exactly
-// where the load of opp(i) came from.  Needs 2 S (population stride) bytes
-// of storage element below 2^32 (checked on the host; k_step_compact serves
-// larger domains).
-template <int LAT, int OP, int PREC, int PAT, bool MON>
+// neighbour, no branch and no 64-bit address arithmetic.  In the AA pull the
+// store of direction i goes exactly where the load of opp(i) came from.  Needs
+// 2 S (population stride) bytes of storage element below 2^32 (checked on the
+// host; k_step_compact serves larger domains).
+//
+// What bounds it: memory above 512 MB of state; below, the vector unit (FP16
+// 92% busy) and the scalar prologue in front of the first load.  The shifted
+// words come ready from the records, the edge lanes are written with
+// v_writelane, x + 1's slot is one add with the lane mask as carry, and the tile
+// walk divides by multiplication: FP16 IR 780 -> 629 vector instructions a wave
+// (FP32 PR 888 -> 732, FP64 IR 672 -> 530) and 100 scalar ones fewer.  Packs of
+// porosity 0.75, us a step: 146 x 87 x 144 D3Q27 FP16 40.1 -> 34.0, 96^3 FP32
+// PR 28.2 -> 25.9, 113 x 67 x 58 D3Q19 FP32 10.7 -> 9.5, FP64 1% or less.
+// LANES: flags and edges formed per lane as before.  Streamed FP32 and FP16
+// states (above 512 MB) keep it: the 256^3 FP32 and 384^3 FP16 packs ran 1%
+// slower with the short form (2192 -> 2214 and 4307 -> 4345 us for 4 steps),
+// whatever the tile, the pace of the loads or the registers.
+template <int LAT, int OP, int PREC, int PAT, bool MON, bool LANES>
 __global__ __launch_bounds__(kMaxBlockThreads) void k_step_rows(const StepArgs a, const SegRec* __restrict__ recs)
 {
     using L = Lattice<LAT>;
@@ -471,8 +525,7 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_step_rows(const StepArgs a
     using C = typename Store<PREC>::C;
     using T = typename Store<PREC>::T;
     static_assert(PAT == PAT_AB || PAT == PAT_AA_PULL, "neighbour phases only");
-    constexpr int SH = sizeof(S) == 8 ? 3 : sizeof(S) == 4 ? 2 : 1;
-    // keep the 27 load offsets for the stores (reduced precision has the
+    // keep the 27 load places for the stores (reduced precision has the
     // registers to spare) or rebuild them after the collision (FP64)
     constexpr bool KEEP = sizeof(S) < 8;
 
@@ -480,20 +533,29 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_step_rows(const StepArgs a
     if (tile >= a.ntiles) return;  // whole block leaves together
 
     const int lane = threadIdx.x & 63;
-    const int sx = a.tx >> 6;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int ly = (wv / sx) % a.ty;
-    const int lz = (wv / sx) / a.ty;
-    int ttx, tty, ttz;
-    tile_coords(a, tile, ttx, tty, ttz);
-    const int seg = ttx * sx + wv % sx;
+    int ly, lz, ttx, tty, ttz, seg;
+    if constexpr (LANES) {
+        const int sx = a.tx >> 6;
+        ly = (wv / sx) % a.ty;
+        lz = (wv / sx) / a.ty;
+        tile_coords_slow(a, tile, ttx, tty, ttz);
+        seg = ttx * sx + wv % sx;
+    } else {
+        const int lsx = a.tx == 256 ? 2 : a.tx == 128 ? 1 : 0;
+        const int wyz = wv >> lsx;
+        lz = (int)(((uint32_t)wyz * a.ty_inv) >> 16);
+        ly = wyz - lz * a.ty;
+        tile_coords(a, tile, ttx, tty, ttz);
+        seg = (ttx << lsx) + (wv & ((1 << lsx) - 1));
+    }
     const int x0 = seg * 64;
     const int y = tty * a.ty + ly;
     const int z = ttz * a.tz + lz;
     const bool wave_in = (y < a.ny) && (z < a.nz) && (x0 < a.nx);
+    // a wave past the box edge reads the last row's records and keeps nothing
     const int yc = min(y, a.ny - 1), zc = min(z, a.nz - 1), sc = min(seg, a.W - 1);
-    const uint64_t keep = wave_in ? ~0ull : 0ull;
-    const int lastbit = min(63, a.nx - 1 - x0);
+    const int lastbit = min(63, a.nx - 1 - sc * 64);
 
     uint64_t wl[9], wm[9], wr[9];
     uint32_t im[9], rl[9], rr[9];
@@ -504,44 +566,65 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_step_rows(const StepArgs a
         if (D == 2 && r / 3 != 1) continue;
         const SegRec* rp = recs + rec_row(yc + r % 3 - 1, zc + r / 3 - 1, a.ny) * a.W + sc;
         wm[r] = rp->bits;
+        if constexpr (!LANES) {
+            wl[r] = (rp->bits << 1) | rp->lbit;
+            wr[r] = (rp->bits >> 1) | rp->rword;
+        }
         im[r] = rp->base;
         rl[r] = rp->lidx;
         rr[r] = rp->ridx;
     }
+    if constexpr (LANES) {
+#pragma unroll
+        for (int r = 0; r < 9; ++r) {
+            if (D == 2 && r / 3 != 1) continue;
+            const uint64_t mb = wave_in ? wm[r] : 0ull;
+            const uint64_t lf = (wave_in && rl[r] != kNoSlot) ? 1ull : 0ull;
+            const uint64_t rf = (wave_in && rr[r] != kNoSlot) ? 1ull : 0ull;
+            wm[r] = uniform64(mb);
+            wl[r] = uniform64((mb << 1) | lf);
+            wr[r] = uniform64((mb >> 1) | (rf << lastbit));
+        }
+    }
 #pragma unroll
     for (int r = 0; r < 9; ++r) {
         if (D == 2 && r / 3 != 1) continue;
-        const uint64_t mb = wm[r] & keep;
-        const uint64_t lf = (wave_in && rl[r] != kNoSlot) ? 1ull : 0ull;
-        const uint64_t rf = (wave_in && rr[r] != kNoSlot) ? 1ull : 0ull;
-        wm[r] = uniform64(mb);
-        wl[r] = uniform64((mb << 1) | lf);
-        wr[r] = uniform64((mb >> 1) | (rf << lastbit));
-        im[r] += __builtin_amdgcn_mbcnt_hi((uint32_t)(mb >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mb, 0u));
+        im[r] += __builtin_amdgcn_mbcnt_hi((uint32_t)(wm[r] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)wm[r], 0u));
     }
-    const bool active = (wm[4] >> lane) & 1;
+    const bool active = wave_in && ((wm[4] >> lane) & 1);
     const uint32_t k = im[4];
     const uint32_t St = (uint32_t)a.S;
-    const uint32_t pair_bytes = (uint32_t)(2 * a.S * (int64_t)sizeof(S));
-    const uint64_t not_first = ~1ull;
+    // the same in a vector register, apart from the scalar one: used in both
+    // roles, one value drags the scalar address arithmetic to the vector unit
+    uint32_t vSt = St;
+    asm("" : "+v"(vSt));
+    const uint32_t kS = k + vSt;
     const uint64_t not_last = uniform64(~((1ull << 63) | (1ull << lastbit)));
 
-    // element offset, within the descriptor of pair {i, opp(i)}, of the
+    // element index, within the descriptor of pair {i, opp(i)}, of the
     // population direction i pulls: the slot of x - c_i in array opp(i)
     // (AA) / i (A/B) when that node is fluid, else the node's own slot in
-    // array i (AA) / opp(i) (A/B)
+    // array i (AA) / opp(i) (A/B).  The slot of x - 1 is im - 1 but for lane 0,
+    // that of x + 1 is im + [x fluid] but for the segment's last node.
     auto load_elem = [&](int i) -> uint32_t {
         if (i == 0) return k;
         const int o = opp(i), lo = i < o ? i : o;
         const int r = (1 - L::cy[i]) + 3 * (1 - L::cz[i]);  // row of x - c_i
         const int dx = -L::cx[i];
         const int dn = PAT == PAT_AB ? i : o, db = PAT == PAT_AB ? o : i;
-        uint32_t nb;  // slot of x - c_i
-        if (dx == 0) nb = im[r];
-        else if (dx < 0) nb = lane_pick(not_first, im[r] - 1u, rl[r]);
-        else nb = lane_pick(not_last, lane_pick(wm[r], im[r] + 1u, im[r]), rr[r]);
+        const uint32_t up = dn == lo ? 0u : St, vup = dn == lo ? 0u : vSt;
+        uint32_t nb;  // place of x - c_i
+        if constexpr (LANES) {
+            if (dx == 0) nb = im[r];
+            else if (dx < 0) nb = lane_pick(~1ull, im[r] - 1u, rl[r]);
+            else nb = lane_pick(not_last, lane_pick(wm[r], im[r] + 1u, im[r]), rr[r]);
+            return lane_pick(dx < 0 ? wl[r] : dx == 0 ? wm[r] : wr[r], nb + up, db == lo ? k : k + St);
+        }
+        if (dx == 0) nb = im[r] + vup;
+        else if (dx < 0) nb = write_lane(rl[r] + up, 0, im[r] + (vup - 1u));
+        else nb = write_lane(rr[r] + up, lastbit, add_bit(im[r], vup, wm[r]));
         const uint64_t fl = dx < 0 ? wl[r] : dx == 0 ? wm[r] : wr[r];
-        return lane_pick(fl, dn == lo ? nb : nb + St, db == lo ? k : k + St);
+        return lane_pick(fl, nb, db == lo ? k : kS);
     };
 
     C h[Q];
@@ -556,9 +639,9 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_step_rows(const StepArgs a
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
             const int o = opp(i), lo = i < o ? i : o;
-            const uint32_t e = load_elem(i) << SH;
+            const uint32_t e = load_elem(i);
             if constexpr (KEEP) off[i] = e;
-            h[i] = decode<PREC>(buf_ld<S>(pop_rsrc(A + (int64_t)lo * a.S, pair_bytes), e), L::w[i], a.h16_scale);
+            h[i] = decode<PREC>(buf_ld<S>(pop_rsrc(A + (int64_t)lo * a.S, 2 * St), e), L::w[i], a.h16_scale);
         }
         if constexpr (has_tau(OP)) tau_prev = (C)((const T*)a.tau)[k];
 
@@ -575,11 +658,11 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_step_rows(const StepArgs a
         for (int i = 0; i < Q; ++i) {
             const S v = encode<PREC>(h[i], L::w[i], a.h16_inv);
             if constexpr (PAT == PAT_AB) {
-                buf_st(v, pop_rsrc(B + (int64_t)i * a.S, pair_bytes / 2), k << SH);
+                buf_st(v, pop_rsrc(B + (int64_t)i * a.S, St), k);
             } else {
                 const int o = opp(i), lo = i < o ? i : o;
-                const uint32_t e = KEEP ? off[o] : (load_elem(o) << SH);
-                buf_st(v, pop_rsrc(B + (int64_t)lo * a.S, pair_bytes), e);
+                const uint32_t e = KEEP ? off[o] : load_elem(o);
+                buf_st(v, pop_rsrc(B + (int64_t)lo * a.S, 2 * St), e);
             }
         }
         if constexpr (has_tau(OP)) ((T*)a.tau)[k] = (T)pr.tau_p;
@@ -593,12 +676,13 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_step_rows(const StepArgs a
 // geometry at all.  One thread per fluid slot, 256 slots per block: every
 // lane is busy and each direction is one contiguous run per wavefront.
 // NT: non-temporal loads and stores, for states larger than the caches
-// (a cache-resident state would only lose its hits).  Those walk the slots in
-// one sequence from the end, which the pull left last (eight sequences, one
-// per XCD, cost 4% in FP64 and 7% in FP16); smaller states take the pull's
-// eight ranges, each XCD its own, backwards: what the pull touched last is
-// still cached (a 382 MB tight medium 715 -> 690 us for 4 steps; A/B alternates
-// the direction in the same way, 2 x 179 MB plates 835 -> 771 for 10).
+// (a cache-resident state would only lose its hits).  With rev set (states up
+// to 400 MB) each XCD walks its own one of the pull's eight ranges, backwards:
+// what the pull touched last is still cached (a 382 MB tight medium 715 -> 690
+// us for 4 steps; A/B alternates the direction in the same way, 2 x 179 MB
+// plates 835 -> 771 for 10).  Larger states take the slots in one sequence
+// (eight at a time cost the streamed FP64 phase 4%, FP16 7%; 1% at 500 MB),
+// above 1 GB from the end (0.2 to 0.8% faster there, 1% slower at 550 MB).
 // Monitor partials: one per block.
 template <int LAT, int OP, int PREC, bool MON, bool NT>
 __global__ __launch_bounds__(kMaxBlockThreads) void k_local_slots(const StepArgs a)
@@ -610,7 +694,9 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_local_slots(const StepArgs
     using T = typename Store<PREC>::T;
 
     const int64_t nblk = (a.nfluid + 255) >> 8;
-    const int64_t cb = NT ? nblk - 1 - blockIdx.x : xcd_place(blockIdx.x, a.slot_bpx, a.rev);
+    const int64_t cb = !a.rev ? (int64_t)blockIdx.x
+                       : NT   ? nblk - 1 - blockIdx.x
+                              : xcd_place(blockIdx.x, a.slot_bpx, 1);
     if (cb < 0 || cb >= nblk) return;  // whole block leaves together
     const int64_t k = cb * 256 + threadIdx.x;
     const bool active = k < a.nfluid;
@@ -837,8 +923,11 @@ static hipError_t go_step(int layout, const StepArgs& a, hipStream_t s)
         }
     } else if (layout == LAYOUT_COMPACT) {
         if constexpr (PAT != PAT_AA_LOCAL) {
-            if (a.buf_rows)
-                hipLaunchKernelGGL((k_step_rows<LAT, OP, PREC, PAT, MON>), grid, dim3(threads), 0, s, a, a.recs);
+            if (a.buf_rows && PREC != PREC_F64 && a.stream_hint)
+                hipLaunchKernelGGL((k_step_rows<LAT, OP, PREC, PAT, MON, PREC != PREC_F64>), grid, dim3(threads), 0, s,
+                                   a, a.recs);
+            else if (a.buf_rows)
+                hipLaunchKernelGGL((k_step_rows<LAT, OP, PREC, PAT, MON, false>), grid, dim3(threads), 0, s, a, a.recs);
             else
                 hipLaunchKernelGGL((k_step_compact<LAT, OP, PREC, PAT, MON>), grid, dim3(threads), 0, s, a, a.recs);
         }
