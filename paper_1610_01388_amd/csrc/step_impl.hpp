@@ -425,12 +425,14 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_step_compact(const StepArg
 
 // Per-lane choice by a wave-uniform lane mask: bit `lane` of mask set gives
 // a, clear gives b -- one v_cndmask_b32 that reads the mask straight from a
-// scalar register pair (no per-lane bit extraction).
+// scalar register pair (no per-lane bit extraction).  By the builtin and not
+// by inline assembly: gfx950 needs two wait states between a vector
+// instruction that writes a scalar register (the reload of a spilled mask) and
+// a vector instruction that reads it, and the compiler places them only for
+// instructions that it knows.
 __device__ __forceinline__ uint32_t lane_pick(uint64_t mask, uint32_t a, uint32_t b)
 {
-    uint32_t r;
-    asm("v_cndmask_b32 %0, %1, %2, %3" : "=v"(r) : "v"(b), "v"(a), "s"(mask));
-    return r;
+    return __builtin_amdgcn_inverse_ballot_w64(mask) ? a : b;
 }
 
 // A wave-uniform 64-bit value marked as such (kept in scalar registers).
@@ -480,14 +482,10 @@ __device__ __forceinline__ void buf_st(_Float16 v, __amdgpu_buffer_rsrc_t r, uin
 // old with the wave-uniform v in the given lane
 __device__ uint32_t write_lane(uint32_t v, uint32_t lane, uint32_t old) __asm("llvm.amdgcn.writelane.i32");
 
-// a + b + (bit `lane` of mask): one v_addc_co_u32 that takes the lane mask as
-// its carry.
+// a + b + (bit `lane` of mask), the mask wave-uniform.
 __device__ __forceinline__ uint32_t add_bit(uint32_t a, uint32_t b, uint64_t mask)
 {
-    uint32_t r;
-    uint64_t carry;
-    asm("v_addc_co_u32 %0, %1, %2, %3, %4" : "=v"(r), "=s"(carry) : "v"(a), "v"(b), "s"(mask));
-    return r;
+    return a + b + (__builtin_amdgcn_inverse_ballot_w64(mask) ? 1u : 0u);
 }
 
 // Compact layout, neighbour phases (AA pull, A/B), row-segment waves with
@@ -506,7 +504,7 @@ __device__ __forceinline__ uint32_t add_bit(uint32_t a, uint32_t b, uint64_t mas
 // What bounds it: memory above 512 MB of state; below, the vector unit (FP16
 // 92% busy) and the scalar prologue in front of the first load.  The shifted
 // words come ready from the records, the edge lanes are written with
-// v_writelane, x + 1's slot is one add with the lane mask as carry, and the tile
+// v_writelane, x + 1's slot adds the lane mask's bit, and the tile
 // walk divides by multiplication: FP16 IR 780 -> 629 vector instructions a wave
 // (FP32 PR 888 -> 732, FP64 IR 672 -> 530) and 100 scalar ones fewer.  Packs of
 // porosity 0.75, us a step: 146 x 87 x 144 D3Q27 FP16 40.1 -> 34.0, 96^3 FP32
