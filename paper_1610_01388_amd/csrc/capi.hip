@@ -239,7 +239,9 @@ Coll<C> make_coll(const lbm_rheology& r)
     c.sigma_y = (C)r.sigma_y;
     c.m = (C)r.m;
     c.gamma_c = (C)(r.gamma_c > 0 ? r.gamma_c : 1e-8);
-    c.lambda = (C)r.lambda_trt;
+    // far past the limit of a large magic number (tau_odd -> infinity), yet
+    // finite: the FP64 relaxation multiplies tau_odd by the body force
+    c.lambda = (C)std::min(r.lambda_trt, 1e100);
     for (int a = 0; a < 3; ++a) c.g[a] = (C)r.g[a];
     c.sqrt2_sy = (C)(std::sqrt(2.0) * r.sigma_y);
     c.ir_a = (C)((6.0 * r.nu_p - 1.0) / (1.0 + 6.0 * r.nu_p));
