@@ -317,10 +317,25 @@ int lbm_get_tile_order(lbm_domain* dom, int32_t* brick_rows, int32_t* brick_plan
 /* Select the compact layout's neighbour-phase kernel (lbm_pull_form); tiles
  * and tile order apply to ROWS only.  LBM_EINVAL for another value.  The
  * dense layout ignores the setting.  Timing only, never results.  The
- * getter reports the kernel in effect (SLOTS or ROWS; AUTO resolved with
- * the current mask). */
+ * getter reports the kernel of single steps (SLOTS or ROWS; AUTO resolved
+ * with the current mask); lbm_get_steps_per_launch tells whether several steps
+ * share a launch.  Setting SLOTS or ROWS keeps to single steps. */
 int lbm_set_pull_form(lbm_domain* dom, int32_t form);
 int lbm_get_pull_form(lbm_domain* dom, int32_t* form);
+/* Steps per launch of a small domain.  0 (default): by a time model, several
+ * where AUTO takes them (lbm_pull_form).  1: never several.  An even number up
+ * to 4096: that many, whatever the kernel form and tile, each block holding a
+ * tile of cx x cy x cz nodes (0: the whole axis) and a halo of as many nodes as
+ * steps on every cut axis; LBM_EINVAL unless the domain is AA and compact,
+ * without MRT and FP64 redo, the tile with its halo fits the local memory of a
+ * compute unit (the whole domain in one tile: also at most a block's threads)
+ * and a second copy of the populations the staging area.  A selection that a
+ * new mask makes too large leaves the choice to the model.  Timing only, never
+ * results.  The getter reports what is in effect: 1 and zeros, or the steps and
+ * tile; odd steps and monitor steps still run one at a time by the kernel of
+ * lbm_get_pull_form. */
+int lbm_set_steps_per_launch(lbm_domain* dom, int32_t steps, int32_t cx, int32_t cy, int32_t cz);
+int lbm_get_steps_per_launch(lbm_domain* dom, int32_t* steps, int32_t* cx, int32_t* cy, int32_t* cz);
 /* Time candidate tile shapes (compact layout: and both neighbour-phase
  * kernels, and several steps per launch where AUTO takes them) on the bound
  * buffers (the state is saved and restored around the trial steps) and keep the fastest; synchronises. */

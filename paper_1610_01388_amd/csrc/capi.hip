@@ -158,9 +158,9 @@ struct lbm_domain {
     size_t lds_bytes = 0;    // LDS a block may use and CUs of the bound GPU
     int cus = 0;
     struct {
-        int steps = 0;       // per launch; 0: the per-step kernels are faster
+        int steps = 0;       // per launch; 0: per-step kernels
         int c[3] = {0, 0, 0};  // tile
-    } multi;
+    } multi, multi_set;      // in use; as selected by the caller (steps 0: by the time model, 1: never)
 };
 
 namespace {
@@ -452,6 +452,9 @@ int run_steps(lbm_domain* dm, int64_t nsteps, hipStream_t st)
 // several steps per launch (k_multi)
 // ---------------------------------------------------------------------------
 
+// Most steps of a launch that holds the whole domain in one block.
+constexpr int kMultiBoxSteps = 4096;
+
 // LDS bytes k_multi keeps per node of its box: populations, relaxation time,
 // neighbour mask, slot (domains with solids) and fluid flag.
 size_t multi_node_bytes(const lbm_domain* dm)
@@ -483,11 +486,31 @@ void multi_box(const lbm_domain* dm, const int (&c)[3], int steps, int (&h)[3], 
     }
 }
 
+// Whether k_multi has kernels for this domain's steps.
+bool multi_able(const lbm_domain* dm)
+{
+    if (dm->d.scheme != LBM_AA || dm->d.layout != LBM_COMPACT || dm->Nf < 1 || dm->cus < 1) return false;
+    if (kernel_op(dm->r) & OP_MRT) return false;
+    return dm->d.precision == LBM_FP64 || !dm->r.fp64_fallback;
+}
+
 // Most nodes of a domain that one block may hold whole.
 int multi_box_nodes(const lbm_domain* dm)
 {
     int n = 0;
     return launch_multi(dm->d.lattice, dm->r.op, dm->d.precision, MultiArgs{}, 0, nullptr, &n) == hipSuccess ? n : 0;
+}
+
+// Whether steps (even, at least 2) of tile c fit one launch: the box in LDS,
+// the second copy in the staging area, the grid's threads below 2^32.
+bool multi_fits(const lbm_domain* dm, const int (&c)[3], int steps)
+{
+    int h[3];
+    int64_t M, tiles;
+    multi_box(dm, c, steps, h, M, tiles);
+    if ((M + 3) / 4 * 4 * multi_node_bytes(dm) > dm->lds_bytes) return false;
+    if (tiles == 1) return dm->N <= multi_box_nodes(dm);
+    return multi_stride(dm) > 0 && tiles < ((int64_t)1 << 22) - 8;
 }
 
 // Time model behind the choice, microseconds, fitted to 900 runs on D2Q9,
@@ -501,8 +524,8 @@ double multi_cost(const lbm_domain* dm, const int (&c)[3], int steps)
 {
     int h[3];
     int64_t M, tiles;
+    if (!multi_fits(dm, c, steps)) return 1e30;
     multi_box(dm, c, steps, h, M, tiles);
-    if ((M + 3) / 4 * 4 * multi_node_bytes(dm) > dm->lds_bytes) return 1e30;
     const bool solve = dm->r.op == LBM_PRI || dm->r.op == LBM_IRHB;
     const double work = (dm->r.op == LBM_PRI ? 4.0 : solve ? 3.0 : dm->r.op == LBM_PR ? 1.5 : 1.0) * (dm->d.precision == LBM_FP16 ? 1.3 : 1.0);
     const double wave = (0.15 + 0.015 * dm->Q) * work, lat = 0.25 + 0.036 * dm->Q;
@@ -530,23 +553,23 @@ double steps_cost(const lbm_domain* dm)
 // Choose tile and steps per launch, or none: k_multi has to promise a fifth
 // less than the per-step kernels.  Tiles cut the axes evenly into parts of
 // about 4 to 32 nodes (or span them); the halo's redundant updates grow with
-// the steps, the launches and loads they share shrink.
+// the steps, the launches and loads they share shrink.  A selection by the
+// caller holds while it fits (a mask with solids takes more LDS per node).
 void plan_multi(lbm_domain* dm)
 {
     dm->multi.steps = 0;
-    if (dm->d.scheme != LBM_AA || dm->d.layout != LBM_COMPACT || dm->Nf < 1 || dm->cus < 1) return;
-    if (kernel_op(dm->r) & OP_MRT) return;
-    if (dm->d.precision != LBM_FP64 && dm->r.fp64_fallback) return;
+    if (!multi_able(dm) || dm->multi_set.steps == 1) return;
+    if (dm->multi_set.steps > 1 && multi_fits(dm, dm->multi_set.c, dm->multi_set.steps)) {
+        dm->multi = dm->multi_set;
+        return;
+    }
     const int n[3] = {dm->d.nx, dm->d.ny, dm->d.nz};
     double best = 0.8 * steps_cost(dm);
-    if (dm->N <= multi_box_nodes(dm)) {
-        const int c[3] = {n[0], n[1], n[2]};
-        const double us = multi_cost(dm, c, 64);  // no halo: the cost per step falls with the steps
-        if (us < best) {
-            best = us;
-            dm->multi.steps = 4096;
-            std::copy(c, c + 3, dm->multi.c);
-        }
+    const double whole = multi_cost(dm, n, 64);  // no halo: the cost per step falls with the steps
+    if (whole < best) {
+        best = whole;
+        dm->multi.steps = kMultiBoxSteps;
+        std::copy(n, n + 3, dm->multi.c);
     }
     if (multi_stride(dm) == 0) return;
     std::vector<int> cut[3];
@@ -621,13 +644,21 @@ int launch_multi_steps(lbm_domain* dm, int steps, bool back, hipStream_t st)
     return LBM_OK;
 }
 
+// Whether launches of several steps are in use: on the caller's selection, or
+// by the time model for the default kernel form and walk.  Monitor intervals up
+// to 4 leave no four steps between two records; from 5 on it is never slower.
+bool multi_on(const lbm_domain* dm)
+{
+    if (dm->multi.steps == 0) return false;
+    if (dm->multi_set.steps > 1) return true;
+    return !dm->tile_set && dm->pull_form == LBM_PULL_AUTO && (dm->mon_k == 0 || dm->mon_k > 4);
+}
+
 // Enqueue nsteps steps: by k_multi where the plan says so (between monitor
 // steps, from the post-collision phase), by the per-step kernels otherwise.
 int advance(lbm_domain* dm, int64_t nsteps, hipStream_t st)
 {
-    const bool on = dm->multi.steps > 0 && !dm->tile_set && dm->pull_form == LBM_PULL_AUTO &&
-                    (dm->mon_k == 0 || dm->mon_k > 4);
-    if (!on) return run_steps(dm, nsteps, st);
+    if (!multi_on(dm)) return run_steps(dm, nsteps, st);
     int rc;
     while (nsteps > 0) {
         int64_t n = nsteps;  // steps that end at the next monitor step
@@ -1215,6 +1246,44 @@ int lbm_get_pull_form(lbm_domain* dm, int32_t* form)
 {
     if (!dm || !form) return fail(LBM_EINVAL, "NULL argument");
     *form = pull_slots(dm) ? LBM_PULL_SLOTS : LBM_PULL_ROWS;
+    return LBM_OK;
+}
+
+int lbm_set_steps_per_launch(lbm_domain* dm, int32_t steps, int32_t cx, int32_t cy, int32_t cz)
+{
+    int rc = need_bound(dm);
+    if (rc) return rc;
+    if (steps < 0 || (steps > 1 && steps % 2) || steps > kMultiBoxSteps)
+        return fail(LBM_EINVAL, "steps per launch must be 0, 1 or an even number up to %d", kMultiBoxSteps);
+    decltype(dm->multi_set) want;
+    want.steps = steps;
+    if (steps > 1) {
+        const int n[3] = {dm->d.nx, dm->d.ny, dm->d.nz}, c[3] = {cx, cy, cz};
+        if (!multi_able(dm))
+            return fail(LBM_EINVAL, "several steps per launch need AA, the compact layout, a fluid node, no MRT and no FP64 redo");
+        for (int a = 0; a < 3; ++a) {
+            if (c[a] < 0 || c[a] > n[a]) return fail(LBM_EINVAL, "tile %dx%dx%d outside the domain", cx, cy, cz);
+            want.c[a] = c[a] ? c[a] : n[a];
+        }
+        if (!multi_fits(dm, want.c, steps))
+            return fail(LBM_EINVAL, "%d steps of tile %dx%dx%d do not fit one launch", steps, want.c[0], want.c[1], want.c[2]);
+    }
+    dm->multi_set = want;
+    dm->gen++;
+    plan_multi(dm);
+    return LBM_OK;
+}
+
+int lbm_get_steps_per_launch(lbm_domain* dm, int32_t* steps, int32_t* cx, int32_t* cy, int32_t* cz)
+{
+    int rc = need_bound(dm);
+    if (rc) return rc;
+    if (!steps || !cx || !cy || !cz) return fail(LBM_EINVAL, "NULL argument");
+    const bool on = multi_on(dm);
+    *steps = on ? dm->multi.steps : 1;
+    *cx = on ? dm->multi.c[0] : 0;
+    *cy = on ? dm->multi.c[1] : 0;
+    *cz = on ? dm->multi.c[2] : 0;
     return LBM_OK;
 }
 

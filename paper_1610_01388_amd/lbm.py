@@ -71,6 +71,7 @@ EXPORTS = ["lbm_last_error", "lbm_lattice_info", "lbm_query_sizes", "lbm_create"
            "lbm_step", "lbm_set_graph_steps", "lbm_time", "lbm_set_monitor_interval", "lbm_read_history", "lbm_monitors",
            "lbm_set_umax_limit", "lbm_monitors_async", "lbm_read_moments", "lbm_save", "lbm_load", "lbm_check_checkpoint", "lbm_set_tile",
            "lbm_get_tile", "lbm_set_tile_order", "lbm_get_tile_order", "lbm_set_pull_form", "lbm_get_pull_form",
+           "lbm_set_steps_per_launch", "lbm_get_steps_per_launch",
            "lbm_autotune", "lbm_destroy",
            "lbm_batch_query_sizes", "lbm_batch_create", "lbm_batch_bind", "lbm_batch_init_equilibrium",
            "lbm_batch_write_populations", "lbm_batch_read_populations", "lbm_batch_read_moments",
@@ -130,6 +131,8 @@ def load_library(path: str = LIB_PATH):
         "lbm_get_tile_order": ([vp, i32p, i32p], ctypes.c_int),
         "lbm_set_pull_form": ([vp, i32], ctypes.c_int),
         "lbm_get_pull_form": ([vp, i32p], ctypes.c_int),
+        "lbm_set_steps_per_launch": ([vp, i32, i32, i32, i32], ctypes.c_int),
+        "lbm_get_steps_per_launch": ([vp, i32p, i32p, i32p, i32p], ctypes.c_int),
         "lbm_autotune": ([vp, i32], ctypes.c_int),
         "lbm_destroy": ([vp], ctypes.c_int),
         "lbm_batch_query_sizes": ([ctypes.POINTER(lbm_desc), ctypes.POINTER(lbm_rheology), i32,
@@ -330,6 +333,16 @@ def lbm_get_pull_form(h):
     return {v: k for k, v in PULL_FORMS.items()}.get(f.value, f.value)
 
 
+def lbm_set_steps_per_launch(h, steps, cx=0, cy=0, cz=0):
+    _check(load_library().lbm_set_steps_per_launch(h, int(steps), int(cx), int(cy), int(cz)))
+
+
+def lbm_get_steps_per_launch(h):
+    v = [ctypes.c_int32() for _ in range(4)]
+    _check(load_library().lbm_get_steps_per_launch(h, *[ctypes.byref(x) for x in v]))
+    return v[0].value, tuple(x.value for x in v[1:])
+
+
 def lbm_autotune(h, trial_steps=10):
     _check(load_library().lbm_autotune(h, int(trial_steps)))
 
@@ -470,6 +483,15 @@ class Domain:
 
     def pull_form(self):
         return lbm_get_pull_form(self.h)
+
+    def set_steps_per_launch(self, steps, tile=(0, 0, 0)):
+        """0: by the library's time model, 1: one, even: that many of this
+        tile (0: the whole axis)."""
+        lbm_set_steps_per_launch(self.h, steps, *tile)
+
+    def steps_per_launch(self):
+        """(steps, tile) in effect; (1, (0, 0, 0)) for single steps."""
+        return lbm_get_steps_per_launch(self.h)
 
     def autotune(self, trial_steps=10):
         lbm_autotune(self.h, trial_steps)
