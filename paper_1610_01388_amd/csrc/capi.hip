@@ -154,7 +154,6 @@ struct lbm_domain {
     uint64_t graph_gen = 0;  // gen the graph was captured at
     double* scratch = nullptr;  // this GPU's allocation-free monitor scratch (resolved by lbm_bind)
     // several steps per launch (small AA domains, compact layout)
-    bool tile_set = false;   // tile or order chosen by the caller: keep the per-step kernels
     size_t lds_bytes = 0;    // LDS a block may use and CUs of the bound GPU
     int cus = 0;
     struct {
@@ -204,7 +203,7 @@ int pow2ceil(int v)
     return p;
 }
 
-void default_tile(lbm_domain* dm)
+void default_tile(const lbm_domain* dm, int& tx, int& ty, int& tz)
 {
     if (dm->d.layout == LBM_COMPACT) {
         // up to 4 adjacent 64-node segments of one row per block (their shared
@@ -213,21 +212,18 @@ void default_tile(lbm_domain* dm)
         // segments so that no wavefront sits past the row end (384 wide: 2),
         // the other waves over y, z
         const int sx = dm->L.W % 4 == 0 ? 4 : dm->L.W % 2 == 0 ? 2 : 1;
-        dm->tx = 64 * sx;
-        dm->ty = std::min(pow2ceil(dm->d.ny), 4 / sx);
-        dm->tz = dm->D == 3 ? std::min(pow2ceil(dm->d.nz), 4 / (sx * dm->ty)) : 1;
+        tx = 64 * sx;
+        ty = std::min(pow2ceil(dm->d.ny), 4 / sx);
+        tz = dm->D == 3 ? std::min(pow2ceil(dm->d.nz), 4 / (sx * ty)) : 1;
         return;
     }
-    int tx = std::min(pow2ceil(dm->d.nx), 64);
-    int ty = std::min(pow2ceil(dm->d.ny), 256 / tx);
-    int tz = dm->D == 3 ? std::min(pow2ceil(dm->d.nz), 256 / (tx * ty)) : 1;
+    tx = std::min(pow2ceil(dm->d.nx), 64);
+    ty = std::min(pow2ceil(dm->d.ny), 256 / tx);
+    tz = dm->D == 3 ? std::min(pow2ceil(dm->d.nz), 256 / (tx * ty)) : 1;
     while (tx * ty * tz < 64) {
         if (tx < 64) tx *= 2;
         else ty *= 2;
     }
-    dm->tx = tx;
-    dm->ty = ty;
-    dm->tz = tz;
 }
 
 template <class C>
@@ -299,17 +295,31 @@ NodeArgs node_args(lbm_domain* dm)
     return a;
 }
 
-// Tile-order bricks: whole rows x bry row-blocks x brz planes.  Default for
+// Tile-order bricks: whole rows x bry row-blocks x brz planes, as wanted by the
+// caller (0: default).  Default for
 // the compact layout: a brick holds about 16 tiles per plane (so
 // z-neighbours are ~16 tiles apart in the order) and one slab of planes per
 // XCD; the dense layout walks x, y, z plainly (measured faster there).
-void tile_order(const lbm_domain* dm, int ntx, int nty, int ntz, int& bry, int& brz)
+void tile_order(const lbm_domain* dm, int want_y, int want_z, int ntx, int nty, int ntz, int& bry, int& brz)
 {
     const bool dense = dm->d.layout == LBM_DENSE;  // the dense kernel keeps the plain order by default
-    bry = dm->bry > 0 ? dm->bry : dense ? nty : std::max(1, 16 / std::max(1, ntx));
-    brz = dm->brz > 0 ? dm->brz : dense ? ntz : (ntz + 7) / 8;
+    bry = want_y > 0 ? want_y : dense ? nty : std::max(1, 16 / std::max(1, ntx));
+    brz = want_z > 0 ? want_z : dense ? ntz : (ntz + 7) / 8;
     bry = std::max(1, std::min(bry, nty));
     brz = std::max(1, std::min(brz, ntz));
+}
+
+// Whether the tile and its order are the default ones, selected or not: what
+// the getters report can be set again without another effect.
+bool default_walk(const lbm_domain* dm)
+{
+    int t[3], want[2], now[2];
+    default_tile(dm, t[0], t[1], t[2]);
+    if (dm->tx != t[0] || dm->ty != t[1] || dm->tz != t[2]) return false;
+    const int ntx = (dm->d.nx + t[0] - 1) / t[0], nty = (dm->d.ny + t[1] - 1) / t[1], ntz = (dm->d.nz + t[2] - 1) / t[2];
+    tile_order(dm, 0, 0, ntx, nty, ntz, want[0], want[1]);
+    tile_order(dm, dm->bry, dm->brz, ntx, nty, ntz, now[0], now[1]);
+    return now[0] == want[0] && now[1] == want[1];
 }
 
 Divider make_divider(int64_t d)
@@ -354,7 +364,7 @@ StepArgs step_args(lbm_domain* dm)
     a.ntz = (dm->d.nz + dm->tz - 1) / dm->tz;
     a.ntiles = a.ntx * a.nty * a.ntz;
     a.tiles_per_xcd = (a.ntiles + 7) / 8;
-    tile_order(dm, a.ntx, a.nty, a.ntz, a.bry, a.brz);
+    tile_order(dm, dm->bry, dm->brz, a.ntx, a.nty, a.ntz, a.bry, a.brz);
     {
         const int64_t last_z = a.ntz - (int64_t)((a.ntz - 1) / a.brz) * a.brz;  // planes of the last slab
         const int64_t last_y = a.nty - (int64_t)((a.nty - 1) / a.bry) * a.bry;  // tile rows of the last brick
@@ -651,7 +661,7 @@ bool multi_on(const lbm_domain* dm)
 {
     if (dm->multi.steps == 0) return false;
     if (dm->multi_set.steps > 1) return true;
-    return !dm->tile_set && dm->pull_form == LBM_PULL_AUTO && (dm->mon_k == 0 || dm->mon_k > 4);
+    return default_walk(dm) && dm->pull_form == LBM_PULL_AUTO && (dm->mon_k == 0 || dm->mon_k > 4);
 }
 
 // Enqueue nsteps steps: by k_multi where the plan says so (between monitor
@@ -844,7 +854,7 @@ int lbm_create(const lbm_desc* desc, const lbm_rheology* rh, lbm_domain** out)
     dm->D = lattice_d(desc->lattice);
     dm->N = (int64_t)desc->nx * desc->ny * desc->nz;
     dm->L = layout_of(desc, rh);
-    default_tile(dm);
+    default_tile(dm, dm->tx, dm->ty, dm->tz);
     *out = dm;
     return LBM_OK;
 }
@@ -1204,7 +1214,6 @@ int lbm_set_tile(lbm_domain* dm, int32_t tx, int32_t ty, int32_t tz)
     dm->tx = tx;
     dm->ty = ty;
     dm->tz = tz;
-    dm->tile_set = true;
     dm->gen++;
     return LBM_OK;
 }
@@ -1215,7 +1224,6 @@ int lbm_set_tile_order(lbm_domain* dm, int32_t brick_rows, int32_t brick_planes)
     if (brick_rows < 0 || brick_planes < 0) return fail(LBM_EINVAL, "brick sizes must be >= 0 (0 = default)");
     dm->bry = brick_rows;
     dm->brz = brick_planes;
-    dm->tile_set = true;
     dm->gen++;
     return LBM_OK;
 }
@@ -1226,7 +1234,7 @@ int lbm_get_tile_order(lbm_domain* dm, int32_t* brick_rows, int32_t* brick_plane
     const int ntx = (dm->d.nx + dm->tx - 1) / dm->tx, nty = (dm->d.ny + dm->ty - 1) / dm->ty;
     const int ntz = (dm->d.nz + dm->tz - 1) / dm->tz;
     int bry = 0, brz = 0;
-    tile_order(dm, ntx, nty, ntz, bry, brz);
+    tile_order(dm, dm->bry, dm->brz, ntx, nty, ntz, bry, brz);
     *brick_rows = bry;
     *brick_planes = brz;
     return LBM_OK;
@@ -1335,12 +1343,13 @@ int lbm_autotune(lbm_domain* dm, int32_t trial_steps)
     float best_ms = 1e30f;
     const int keep[3] = {dm->tx, dm->ty, dm->tz};
     const int keep_form = dm->pull_form;
-    const bool keep_set = dm->tile_set;
+    const int keep_order[2] = {dm->bry, dm->brz};
     if (dm->multi.steps > 0 && he == hipSuccess) {
         // several steps per launch, as the default form takes them; even
         // counts, as a long run has them
         const int n = std::max(4, (trial_steps + 3) / 4 * 4);
-        dm->tile_set = false;
+        default_tile(dm, dm->tx, dm->ty, dm->tz);
+        dm->bry = dm->brz = 0;
         dm->pull_form = LBM_PULL_AUTO;
         if (dm->parity != 0) rc = run_steps(dm, 1, dm->stream);
         float ms = 0;
@@ -1351,6 +1360,8 @@ int lbm_autotune(lbm_domain* dm, int32_t trial_steps)
             best_ms = ms * (float)trial_steps / (float)n;
             best = -3;
         }
+        dm->bry = keep_order[0];
+        dm->brz = keep_order[1];
     }
     for (int c = dm->d.layout == LBM_COMPACT ? -1 : 0; c < nc && he == hipSuccess && rc == LBM_OK; ++c) {
         if (c >= 0) {
@@ -1381,7 +1392,6 @@ int lbm_autotune(lbm_domain* dm, int32_t trial_steps)
     dm->ty = keep[1];
     dm->tz = keep[2];
     dm->pull_form = keep_form;
-    dm->tile_set = keep_set;
     const bool ok = rc == LBM_OK && he == hipSuccess;
     if (ok && best >= 0) {
         dm->tx = cand[best][0];
@@ -1390,8 +1400,9 @@ int lbm_autotune(lbm_domain* dm, int32_t trial_steps)
     }
     if (ok && best >= -1 && dm->d.layout == LBM_COMPACT) dm->pull_form = best < 0 ? LBM_PULL_SLOTS : LBM_PULL_ROWS;
     if (ok && best == -3) {
+        default_tile(dm, dm->tx, dm->ty, dm->tz);
+        dm->bry = dm->brz = 0;
         dm->pull_form = LBM_PULL_AUTO;
-        dm->tile_set = false;
     }
     dm->gen++;
     const int rc_load = lbm_load(dm, saved.data(), bytes);

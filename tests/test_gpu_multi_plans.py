@@ -117,3 +117,22 @@ def test_selection_that_a_mask_makes_too_large():
             x.step(21)
         assert (d.steps_per_launch() == (2, (61, 95, 1))) == (mask is None or not mask.any())
         assert same(state(d, "IR"), state(ref, "IR"))
+
+
+def test_default_walk_can_be_set_again():
+    """Several steps per launch go with the default tile and order: another one
+    turns them off, the default (by its values, or 0 for the order) on again."""
+    d = make("D3Q19", (128, 128, 4), (0, 0, 1), "IR", "FP64", None)
+    plan, tile, order = d.steps_per_launch(), d.tile(), d.tile_order()
+    assert plan[0] > 1
+    d.set_tile(*tile)
+    d.set_tile_order(*order)
+    assert d.steps_per_launch() == plan
+    d.set_tile(64, 2, 1)
+    assert d.steps_per_launch()[0] == 1
+    d.set_tile(*tile)
+    assert d.steps_per_launch() == plan
+    d.set_tile_order(1, 1)
+    assert d.steps_per_launch()[0] == 1
+    d.set_tile_order(0, 0)
+    assert d.steps_per_launch() == plan
