@@ -339,8 +339,11 @@ int lbm_get_pull_form(lbm_domain* dom, int32_t* form);
 int lbm_set_steps_per_launch(lbm_domain* dom, int32_t steps, int32_t cx, int32_t cy, int32_t cz);
 int lbm_get_steps_per_launch(lbm_domain* dom, int32_t* steps, int32_t* cx, int32_t* cy, int32_t* cz);
 /* Time candidate tile shapes (compact layout: and both neighbour-phase
- * kernels, and several steps per launch where AUTO takes them) on the bound
- * buffers (the state is saved and restored around the trial steps) and keep the fastest; synchronises. */
+ * kernels, and several steps per launch where AUTO or a selection takes them at
+ * the monitor interval in effect) on the bound buffers and keep the fastest: a
+ * single-step form as if selected, or several steps with AUTO and the default
+ * tile and order.  The state is saved and restored around the trial steps;
+ * synchronises. */
 int lbm_autotune(lbm_domain* dom, int32_t trial_steps);
 
 int lbm_destroy(lbm_domain* dom);

@@ -666,13 +666,15 @@ bool multi_on(const lbm_domain* dm)
 
 // Enqueue nsteps steps: by k_multi where the plan says so (between monitor
 // steps, from the post-collision phase), by the per-step kernels otherwise.
-int advance(lbm_domain* dm, int64_t nsteps, hipStream_t st)
+// gap: the monitor interval to keep clear of (the autotuner's trials record
+// nothing).
+int advance(lbm_domain* dm, int64_t nsteps, hipStream_t st, int gap)
 {
     if (!multi_on(dm)) return run_steps(dm, nsteps, st);
     int rc;
     while (nsteps > 0) {
         int64_t n = nsteps;  // steps that end at the next monitor step
-        if (dm->mon_k > 0) n = dm->t % dm->mon_k == 0 ? 0 : std::min<int64_t>(n, dm->mon_k - dm->t % dm->mon_k);
+        if (gap > 0) n = dm->t % gap == 0 ? 0 : std::min<int64_t>(n, gap - dm->t % gap);
         n -= n % 2;
         if (dm->parity != 0 || n < 4) {
             const int64_t k = std::min<int64_t>(nsteps, dm->parity != 0 ? 1 : 2);
@@ -730,7 +732,7 @@ int build_graph(lbm_domain* dm)
     const int cur = dm->cur, parity = dm->parity;
     const std::vector<int64_t> times = dm->hist_time;
     HIPCHK(hipStreamBeginCapture(dm->cap, hipStreamCaptureModeThreadLocal));
-    const int rc = advance(dm, dm->graph_steps, dm->cap);
+    const int rc = advance(dm, dm->graph_steps, dm->cap, dm->mon_k);
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(dm->cap, &g);
     dm->t = t;
@@ -979,7 +981,7 @@ int lbm_step(lbm_domain* dm, int64_t nsteps)
         if (!graph_ok) {
             int64_t n = nsteps;
             if (G > 0 && dm->t % G != 0) n = std::min<int64_t>(nsteps, G - dm->t % G);
-            if ((rc = advance(dm, n, dm->stream))) return rc;
+            if ((rc = advance(dm, n, dm->stream, dm->mon_k))) return rc;
             nsteps -= n;
             continue;
         }
@@ -1344,17 +1346,24 @@ int lbm_autotune(lbm_domain* dm, int32_t trial_steps)
     const int keep[3] = {dm->tx, dm->ty, dm->tz};
     const int keep_form = dm->pull_form;
     const int keep_order[2] = {dm->bry, dm->brz};
-    if (dm->multi.steps > 0 && he == hipSuccess) {
-        // several steps per launch, as the default form takes them; even
-        // counts, as a long run has them
-        const int n = std::max(4, (trial_steps + 3) / 4 * 4);
+    if (dm->multi.steps > 0 && (mon_k == 0 || mon_k > 4) && he == hipSuccess) {
+        // several steps per launch, as a long run takes them: whole pairs of
+        // launches, or 256 steps of a domain in one block; with records closer
+        // than eight of those, whole monitor intervals (two where their length
+        // is odd)
+        int h[3];
+        int64_t M, tiles;
+        multi_box(dm, dm->multi.c, dm->multi.steps, h, M, tiles);
+        const int pair = tiles == 1 ? 256 : 2 * dm->multi.steps;
+        const int gap = mon_k < 8 * pair ? mon_k : 0;
+        const int unit = gap > 0 ? gap * (1 + gap % 2) : pair;
+        const int64_t n = ((int64_t)trial_steps + unit - 1) / unit * unit;
         default_tile(dm, dm->tx, dm->ty, dm->tz);
         dm->bry = dm->brz = 0;
         dm->pull_form = LBM_PULL_AUTO;
-        if (dm->parity != 0) rc = run_steps(dm, 1, dm->stream);
         float ms = 0;
-        if (rc == LBM_OK && (rc = advance(dm, n, dm->stream)) == LBM_OK &&
-            (he = hipEventRecord(e0, dm->stream)) == hipSuccess && (rc = advance(dm, n, dm->stream)) == LBM_OK &&
+        if ((rc = advance(dm, 2 * unit - dm->t % unit, dm->stream, gap)) == LBM_OK &&
+            (he = hipEventRecord(e0, dm->stream)) == hipSuccess && (rc = advance(dm, n, dm->stream, gap)) == LBM_OK &&
             (he = hipEventRecord(e1, dm->stream)) == hipSuccess && (he = hipEventSynchronize(e1)) == hipSuccess &&
             (he = hipEventElapsedTime(&ms, e0, e1)) == hipSuccess) {
             best_ms = ms * (float)trial_steps / (float)n;
@@ -1398,7 +1407,10 @@ int lbm_autotune(lbm_domain* dm, int32_t trial_steps)
         dm->ty = cand[best][1];
         dm->tz = cand[best][2];
     }
-    if (ok && best >= -1 && dm->d.layout == LBM_COMPACT) dm->pull_form = best < 0 ? LBM_PULL_SLOTS : LBM_PULL_ROWS;
+    if (ok && best >= -1 && dm->d.layout == LBM_COMPACT) {
+        dm->pull_form = best < 0 ? LBM_PULL_SLOTS : LBM_PULL_ROWS;
+        if (dm->multi_set.steps > 1) dm->multi_set.steps = 0;  // selected by hand, and slower
+    }
     if (ok && best == -3) {
         default_tile(dm, dm->tx, dm->ty, dm->tz);
         dm->bry = dm->brz = 0;

@@ -136,3 +136,35 @@ def test_default_walk_can_be_set_again():
     assert d.steps_per_launch()[0] == 1
     d.set_tile_order(0, 0)
     assert d.steps_per_launch() == plan
+
+
+def test_autotune_times_what_will_run():
+    """Monitor intervals up to 4 leave single steps only, so a single-step form
+    is tuned there; else several steps are timed in whole launches whatever the
+    trial's length, and win on small domains."""
+    for lat, dims, per, op in (("D2Q9", (80, 80, 1), (1, 1, 1), "PR"), ("D2Q9", (4, 64, 1), (1, 0, 1), "IR"),
+                               ("D2Q9", (150, 150, 1), (1, 0, 1), "IR")):
+        d = make(lat, dims, per, op, "FP64", None)
+        plan = d.steps_per_launch()
+        assert plan[0] > 1
+        d.step(3)
+        before = state(d, op)
+        for interval, trial in ((0, 1), (0, 10), (7, 10), (40, 10), (100000, 3)):
+            d.set_monitor_interval(interval)
+            d.autotune(trial)
+            assert d.steps_per_launch() == plan, (dims, interval, trial)
+            assert d.time == 3 and same(state(d, op), before)
+        d.set_monitor_interval(3)
+        d.autotune(10)
+        assert d.time == 3 and same(state(d, op), before)
+        d.set_monitor_interval(0)
+        assert d.steps_per_launch()[0] == 1
+        d.close()
+
+
+def test_autotune_drops_a_slow_selection():
+    d = make("D3Q27", (60, 40, 24), (1, 0, 1), "IR", "FP64", None)
+    d.set_steps_per_launch(2, (1, 1, 1))  # 125 nodes updated for one
+    d.autotune(10)
+    assert d.steps_per_launch()[0] == 1
+    d.close()
