@@ -399,13 +399,18 @@ int lbm_batch_get_tiles(lbm_batch* b, int32_t* tiles);
 /* Scheduling in use: tile policy (0 fewest padded nodes, 1 rows at least
  * 64 wide, 2 fixed 64x4x1, 3, the default, runs of 256 consecutive nodes in
  * node order, rows wrapping, reported by lbm_batch_get_tiles as 256x1x1) and
- * work-item order (0, the default, plain order of the list, or chunks as in
- * 1 for an arena that the caches hold; 1 one contiguous chunk of the list per
- * XCD so that neighbouring tiles share an L2). */
+ * work-item order as selected (0 plain order of the list; 1 one contiguous
+ * chunk of the list per XCD so that neighbouring tiles share an L2; 0 also while
+ * nothing is selected, see lbm_batch_get_order). */
 int lbm_batch_get_schedule(lbm_batch* b, int32_t* tile_policy, int32_t* xcd_order);
 /* Choose the scheduling by hand (the state is kept; results do not depend on
  * it).  LBM_EINVAL outside the ranges above.  Synchronises. */
 int lbm_batch_set_schedule(lbm_batch* b, int32_t tile_policy, int32_t xcd_order);
+/* The work-item order alone: 0, 1, or -1 (the default) for chunks while the
+ * arena is below 400 MB and plain order above.  Synchronises.  The getter
+ * reports the selection and the order in effect. */
+int lbm_batch_set_order(lbm_batch* b, int32_t xcd_order);
+int lbm_batch_get_order(lbm_batch* b, int32_t* selected, int32_t* in_effect);
 /* Time every tile policy with both work-item orders on trial_steps steps of
  * the bound batch and keep the fastest; the state is restored.  The device
  * layout does not depend on the choice.  Synchronises. */

@@ -1473,8 +1473,8 @@ struct lbm_batch {
     int grid = 0;
     int policy = 3;  // tile policy: 0 fewest padded nodes (wide rows on ties), 1 prefer 64-wide rows, 2 fixed 64x4x1,
                      // 3 (default) runs of 256 consecutive nodes
-    int xcd = 0;     // work-item order: 1 = one contiguous chunk per XCD, 0 (default) = plain order,
-                     // or chunks for a cache-sized arena (batch_chunks)
+    int xcd = -1;    // work-item order: 0 = plain order, 1 = one contiguous chunk per XCD, -1 (default) = by the
+                     // arena's size (batch_chunks)
     size_t bound_total = 0;  // work-buffer bytes the layout had when bound
 };
 
@@ -1574,12 +1574,12 @@ int batch_plan(lbm_batch* b)
     return LBM_OK;
 }
 
-// Items in one contiguous chunk per XCD: on request (order 1), and in order 0
+// Items in one contiguous chunk per XCD: on request (order 1), and by default
 // while the arena is cache-sized.  Neighbouring items then meet in one L2 from
 // step to step: sweeps of 4 to 160 ducts below 400 MB ran 3 to 28% faster that
 // way (32 MB FP32 14.0 -> 11.3 us a step, 173 MB FP64 59.6 -> 53.7; 57 MB FP64
 // 20.4 -> 20.9 the one that lost), above 400 MB 0 to 3% slower.
-bool batch_chunks(const lbm_batch* b) { return b->xcd != 0 || (double)b->L.pdf < 400e6; }
+bool batch_chunks(const lbm_batch* b) { return b->xcd < 0 ? (double)b->L.pdf < 400e6 : b->xcd != 0; }
 
 // One block per work item, a multiple of 8 in the per-XCD order.
 void batch_set_grid(lbm_batch* b)
@@ -2016,7 +2016,27 @@ int lbm_batch_get_schedule(lbm_batch* b, int32_t* tile_policy, int32_t* xcd_orde
 {
     if (!b || !tile_policy || !xcd_order) return fail(LBM_EINVAL, "NULL argument");
     *tile_policy = b->policy;
-    *xcd_order = b->xcd;
+    *xcd_order = std::max(b->xcd, 0);
+    return LBM_OK;
+}
+
+int lbm_batch_set_order(lbm_batch* b, int32_t xcd_order)
+{
+    int rc = batch_need(b);
+    if (rc) return rc;
+    if (xcd_order < -1 || xcd_order > 1) return fail(LBM_EINVAL, "the work-item order must be -1, 0 or 1");
+    HIPCHK(hipStreamSynchronize(b->stream));
+    b->xcd = xcd_order;
+    batch_set_grid(b);
+    batch_drop_graph(b);
+    return LBM_OK;
+}
+
+int lbm_batch_get_order(lbm_batch* b, int32_t* selected, int32_t* in_effect)
+{
+    if (!b || !selected || !in_effect) return fail(LBM_EINVAL, "NULL argument");
+    *selected = b->xcd;
+    *in_effect = batch_chunks(b) ? 1 : 0;
     return LBM_OK;
 }
 
@@ -2030,7 +2050,7 @@ int lbm_batch_autotune(lbm_batch* b, int32_t trial_steps)
     std::vector<char> pdf(b->L.pdf), tau(b->L.tau);
     HIPCHK(hipMemcpy(pdf.data(), b->pdf, b->L.pdf, hipMemcpyDeviceToHost));
     if (b->L.tau) HIPCHK(hipMemcpy(tau.data(), b->tau, b->L.tau, hipMemcpyDeviceToHost));
-    const int parity = b->parity, mon_k = b->mon_k, keep = b->policy + kBatchPolicies * b->xcd;
+    const int parity = b->parity, mon_k = b->mon_k, keep_policy = b->policy, keep_xcd = b->xcd;
     const int64_t t = b->t;
     const auto times = b->mon_times;
     b->mon_k = 0;
@@ -2039,7 +2059,7 @@ int lbm_batch_autotune(lbm_batch* b, int32_t trial_steps)
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t he = hipEventCreate(&e0);
     if (he == hipSuccess) he = hipEventCreate(&e1);
-    int best = keep;
+    int best = -1;
     float best_ms = 1e30f;
     // candidates: tile policy x work-item order
     for (int cand = 0; cand < 2 * kBatchPolicies && rc == LBM_OK && he == hipSuccess; ++cand) {
@@ -2069,9 +2089,9 @@ int lbm_batch_autotune(lbm_batch* b, int32_t trial_steps)
     }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
-    if (rc != LBM_OK || he != hipSuccess) best = keep;
-    b->policy = best % kBatchPolicies;
-    b->xcd = best / kBatchPolicies;
+    if (rc != LBM_OK || he != hipSuccess) best = -1;
+    b->policy = best < 0 ? keep_policy : best % kBatchPolicies;
+    b->xcd = best < 0 ? keep_xcd : best / kBatchPolicies;
     int rc2 = batch_plan(b);
     if (rc2 == LBM_OK) {
         HIPCHK(hipMemcpy(b->workbuf + b->L.sims, b->sims.data(), sizeof(BatchSim) * b->count, hipMemcpyHostToDevice));

@@ -77,7 +77,7 @@ EXPORTS = ["lbm_last_error", "lbm_lattice_info", "lbm_query_sizes", "lbm_create"
            "lbm_batch_write_populations", "lbm_batch_read_populations", "lbm_batch_read_moments",
            "lbm_batch_set_monitor_interval", "lbm_batch_read_history", "lbm_batch_monitors",
            "lbm_batch_set_graph_steps", "lbm_batch_step", "lbm_batch_time", "lbm_batch_get_tiles",
-           "lbm_batch_get_schedule", "lbm_batch_set_schedule",
+           "lbm_batch_get_schedule", "lbm_batch_set_schedule", "lbm_batch_get_order", "lbm_batch_set_order",
            "lbm_batch_autotune", "lbm_batch_destroy"]
 
 _lib = None
@@ -153,6 +153,8 @@ def load_library(path: str = LIB_PATH):
         "lbm_batch_get_tiles": ([vp, i32p], ctypes.c_int),
         "lbm_batch_get_schedule": ([vp, i32p, i32p], ctypes.c_int),
         "lbm_batch_set_schedule": ([vp, i32, i32], ctypes.c_int),
+        "lbm_batch_get_order": ([vp, i32p, i32p], ctypes.c_int),
+        "lbm_batch_set_order": ([vp, i32], ctypes.c_int),
         "lbm_batch_autotune": ([vp, i32], ctypes.c_int),
         "lbm_batch_destroy": ([vp], ctypes.c_int),
     }
@@ -599,6 +601,16 @@ def lbm_batch_set_schedule(h, tile_policy, xcd_order):
     _check(load_library().lbm_batch_set_schedule(h, int(tile_policy), int(xcd_order)))
 
 
+def lbm_batch_get_order(h):
+    sel, eff = ctypes.c_int32(), ctypes.c_int32()
+    _check(load_library().lbm_batch_get_order(h, ctypes.byref(sel), ctypes.byref(eff)))
+    return sel.value, eff.value
+
+
+def lbm_batch_set_order(h, xcd_order):
+    _check(load_library().lbm_batch_set_order(h, int(xcd_order)))
+
+
 def lbm_batch_autotune(h, trial_steps=10):
     _check(load_library().lbm_batch_autotune(h, int(trial_steps)))
 
@@ -683,8 +695,16 @@ class Batch:
         lbm_batch_autotune(self.h, trial_steps)
 
     def schedule(self):
-        """(tile policy, work-item order) in use."""
+        """(tile policy in use, work-item order as selected)."""
         return lbm_batch_get_schedule(self.h)
+
+    def order(self):
+        """Work-item order (as selected, in effect); selected is -1 while it
+        goes by the arena's size."""
+        return lbm_batch_get_order(self.h)
+
+    def set_order(self, xcd_order):
+        lbm_batch_set_order(self.h, xcd_order)
 
     def set_schedule(self, tile_policy, xcd_order):
         lbm_batch_set_schedule(self.h, tile_policy, xcd_order)
