@@ -148,6 +148,16 @@ def compare(ref, got, axis):
             "unyielded_ref": pr, "unyielded": pg}
 
 
+def kernel_fields(dom, gbs):
+    """Which kernel advances a compact domain, and the share of the peak HBM
+    rate: none where several steps share a launch, since their populations
+    stay on the chip and the algorithmic bytes are not moved."""
+    steps, tile = dom.steps_per_launch()
+    if steps > 1:
+        return {"neighbour_kernel": None, "steps_per_launch": steps, "launch_tile": list(tile), "hbm_frac": None}
+    return {"neighbour_kernel": dom.pull_form(), "steps_per_launch": 1, "hbm_frac": gbs / HBM_PEAK_GBS}
+
+
 def run_form(torch, lbm, name, case, precision, mask, fluid, warmup, steps, ref=None, develop=0, graph=0, **kw):
     """One bench form: from rest, `develop` untimed steps, the moments at that
     time (the accuracy snapshot, compared with `ref` when given), then
@@ -172,7 +182,7 @@ def run_form(torch, lbm, name, case, precision, mask, fluid, warmup, steps, ref=
     if kw.get("fp64_fallback"):
         out["fallback_band"] = kw.get("fallback_band")
     if kw.get("layout", "COMPACT") == "COMPACT":
-        out["neighbour_kernel"] = dom.pull_form()
+        out.update(kernel_fields(dom, gbs))
     if mom is None:
         mom = dom.moments()
     hist = dom.history()
@@ -277,8 +287,8 @@ def precision_study(torch, lbm, inputs, n, horizons, bands):
 
 def run_batch(torch, lbm, cases, precision, warmup, steps, autotune=True, graph_steps=1000):
     """The batched sweep: every case in one batch, stepped by replays of one
-    captured graph of graph_steps persistent launches (one per step); tiles
-    and work-item order picked by the autotuner."""
+    captured graph of graph_steps launches (one per step); tiles and work-item
+    order picked by the autotuner."""
     b = lbm.Batch(cases, precision=precision)
     if autotune:
         b.autotune(10)
