@@ -523,13 +523,13 @@ bool multi_fits(const lbm_domain* dm, const int (&c)[3], int steps)
     return multi_stride(dm) > 0 && tiles < ((int64_t)1 << 22) - 8;
 }
 
-// Time model behind the choice, microseconds, fitted to 900 runs on D2Q9,
-// D3Q19 and D3Q27 ducts of 48^2 to 200^2 nodes (every precision; IR and PR
-// within 13%).  A launch costs 4.1 to 4.7 plus, for each round of blocks over
-// the CUs (15% more when there are several), 2.8 per 100 KB of populations loaded, a latency per step (the
-// dependent chain of one node update) and the vector work of the fullest
-// SIMD: its waves times `wave`.  PRI and IRHB iterate per node; they are
-// counted four and three times the work of IR and kept to one round.
+// Time model of a launch of several steps, microseconds a step; it ranks tiles
+// and step counts.  A launch costs 4.1 to 4.7 plus, for each round of blocks over
+// the CUs (15% more when there are several), 2.8 per 100 KB of populations
+// loaded, a latency per step (the dependent chain of one node update) and the
+// vector work of the fullest SIMD: its waves times `wave`.  PRI and IRHB iterate
+// per node; they are counted four and three times the work of IR and kept to one
+// round.  multi_scale brings it to measured times.
 double multi_cost(const lbm_domain* dm, const int (&c)[3], int steps)
 {
     int h[3];
@@ -550,20 +550,50 @@ double multi_cost(const lbm_domain* dm, const int (&c)[3], int steps)
     return ((double)rounds * (rounds > 1 ? 1.15 : 1.0) * t + 3.8 + 0.035 * dm->Q) / steps;
 }
 
-// The per-step kernels on a cache-resident domain (the same runs, and boxes up
-// to 256 x 256 x 4 and 1000^2): launch and latency, then 5 TB/s, 10 TB/s past
-// 30 MB a step.
-double steps_cost(const lbm_domain* dm)
+// Measured over modelled time of launches of several steps by operator: 3-D and
+// 2-D in FP32 and FP16, then in FP64; 7% more with solids, 26% less for a domain
+// in one block.  Fitted, like steps_cost, to 2500 timings of D2Q9, D3Q19 and
+// D3Q27 domains of 256 to 10^6 nodes, all operators and precisions, without
+// solids and with 10 and 30%, at rest and in strong motion (in the state that
+// suits several steps least): 90% of the times within 14%.
+double multi_scale(const lbm_domain* dm, bool whole)
 {
-    const double mb = 2e-6 * (double)dm->Nf * dm->Q * (double)prec_bytes(dm->d.precision);
-    const double solve = dm->r.op == LBM_IR ? 0.0 : dm->r.op == LBM_PR ? 0.4 : 1.5;
-    return 4.2 + 0.02 * dm->Q + 0.2 * std::min(mb, 30.0) + 0.1 * std::max(mb - 30.0, 0.0) + solve;
+    static const double k[4][4] = {{1.05, 1.01, 1.14, 1.19},   // LBM_PR
+                                   {1.02, 0.92, 1.06, 1.09},   // LBM_IR
+                                   {0.93, 1.03, 1.15, 1.44},   // LBM_PRI
+                                   {1.27, 1.68, 1.20, 1.54}};  // LBM_IRHB
+    return k[dm->r.op][(dm->d.precision == LBM_FP64 ? 2 : 0) + (dm->D == 2 ? 1 : 0)] * (dm->Nf < dm->N ? 1.07 : 1.0) *
+           (whole ? 0.74 : 1.0);
 }
 
-// Choose tile and steps per launch, or none: k_multi has to promise a fifth
-// less than the per-step kernels.  Tiles cut the axes evenly into parts of
-// about 4 to 32 nodes (or span them); the halo's redundant updates grow with
-// the steps, the launches and loads they share shrink.  A selection by the
+// The per-step kernels on a cache-resident domain, microseconds a step: launch
+// and latency, the populations at 6 to 8 TB/s, past 30 MB a step at 4 (3-D) and 9
+// (2-D), and the operator's arithmetic.
+double steps_cost(const lbm_domain* dm)
+{
+    const double mb = 2e-6 * (double)dm->Nf * dm->Q * (double)prec_bytes(dm->d.precision), n = 1e-5 * (double)dm->N;
+    const double op = dm->r.op == LBM_IR    ? 0.0
+                      : dm->r.op == LBM_PR  ? 0.47
+                      : dm->r.op == LBM_PRI ? 1.6 + 0.65 * n
+                                            : 2.65 + 0.75 * n;
+    const bool flat = dm->D == 2;
+    return 2.4 + 0.078 * dm->Q + (flat ? 0.13 : 0.156) * std::min(mb, 30.0) +
+           (flat ? 0.114 : 0.263) * std::max(mb - 30.0, 0.0) + op;
+}
+
+// Share of the single steps' time that several steps have to promise: the rest
+// covers the models' error, which is larger where a per-node solve's iterations
+// depend on the flow.  Of 907 of those domains, every one with 0.97 or more of the
+// single steps' time but three of 1.01 is left out, and 5% of those below 0.85.
+double multi_promise(const lbm_domain* dm)
+{
+    if (dm->r.op == LBM_PR || dm->r.op == LBM_IR) return 0.9;
+    return dm->D == 3 ? 0.75 : dm->r.op == LBM_PRI ? 0.9 : 0.85;
+}
+
+// Choose tile and steps per launch, or none.  Tiles cut the axes evenly into
+// parts of about 4 to 32 nodes (or span them); the halo's redundant updates grow
+// with the steps, the launches and loads they share shrink.  A selection by the
 // caller holds while it fits (a mask with solids takes more LDS per node).
 void plan_multi(lbm_domain* dm)
 {
@@ -574,14 +604,12 @@ void plan_multi(lbm_domain* dm)
         return;
     }
     const int n[3] = {dm->d.nx, dm->d.ny, dm->d.nz};
-    double best = 0.8 * steps_cost(dm);
-    const double whole = multi_cost(dm, n, 64);  // no halo: the cost per step falls with the steps
-    if (whole < best) {
-        best = whole;
-        dm->multi.steps = kMultiBoxSteps;
-        std::copy(n, n + 3, dm->multi.c);
+    auto plan = dm->multi;
+    double best = multi_cost(dm, n, 64);  // whole domain, no halo: the cost per step falls with the steps
+    if (best < 1e30) {
+        plan.steps = kMultiBoxSteps;
+        std::copy(n, n + 3, plan.c);
     }
-    if (multi_stride(dm) == 0) return;
     std::vector<int> cut[3];
     for (int a = 0; a < 3; ++a) {
         if (n[a] <= 64) cut[a].push_back(n[a]);
@@ -600,11 +628,12 @@ void plan_multi(lbm_domain* dm)
                     if (us >= 1e30) break;  // outgrows the LDS, or never fits
                     if (us < best) {
                         best = us;
-                        dm->multi.steps = T;
-                        std::copy(c, c + 3, dm->multi.c);
+                        plan.steps = T;
+                        std::copy(c, c + 3, plan.c);
                     }
                 }
             }
+    if (best * multi_scale(dm, plan.steps == kMultiBoxSteps) < multi_promise(dm) * steps_cost(dm)) dm->multi = plan;
 }
 
 int launch_multi_steps(lbm_domain* dm, int steps, bool back, hipStream_t st)

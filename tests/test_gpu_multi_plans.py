@@ -168,3 +168,17 @@ def test_autotune_drops_a_slow_selection():
     d.autotune(10)
     assert d.steps_per_launch()[0] == 1
     d.close()
+
+
+@pytest.mark.parametrize("lat,dims,op,precision,solids", [
+    ("D3Q19", (128, 128, 4), "IRHB", "FP32", 0.0),  # several / single 1.33
+    ("D2Q9", (500, 500, 1), "IRHB", "FP64", 0.3),   # 1.19
+    ("D2Q9", (500, 500, 1), "PRI", "FP64", 0.3),    # 1.17
+    ("D2Q9", (700, 700, 1), "PR", "FP64", 0.3),     # 1.14
+    ("D2Q9", (800, 800, 1), "IR", "FP64", 0.3)])    # 1.12
+def test_single_steps_where_several_measured_slower(lat, dims, op, precision, solids):
+    N = int(np.prod(dims))
+    d = make(lat, dims, (1, 0, 1) if lat == "D2Q9" else (0, 0, 1), op, precision,
+             random_mask(N, 5, solids) if solids else None)
+    assert d.steps_per_launch()[0] == 1
+    d.close()
