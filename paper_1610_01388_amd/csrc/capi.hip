@@ -188,11 +188,14 @@ int check_tile(const lbm_domain* dm, int tx, int ty, int tz)
 // keeps every lane busy, the row-segment kernel reads the bitmap through the
 // scalar cache but idles the lanes of solid nodes; measured on D3Q27 FP64
 // 256^3 boxes, the row kernel leads from 70% fluid up and the slot kernel
-// below 40% (1.7x at 15%).
+// below 40% (1.7x at 15%).  Rows of a few nodes give more tiles than the work
+// buffer has monitor slots (one per 32 nodes and 64 more): those are left to the
+// slot kernel too.
 bool pull_slots(const lbm_domain* dm)
 {
     if (dm->d.layout != LBM_COMPACT) return false;
-    if (dm->pull_form == LBM_PULL_AUTO) return (double)dm->Nf < 0.45 * (double)dm->N;
+    if (dm->pull_form == LBM_PULL_AUTO)
+        return (double)dm->Nf < 0.45 * (double)dm->N || ntiles_of(dm, dm->tx, dm->ty, dm->tz) > dm->L.max_parts;
     return dm->pull_form == LBM_PULL_SLOTS;
 }
 
@@ -414,7 +417,7 @@ int64_t chunk_nodes(const lbm_domain* dm, size_t bytes_per_node)
 int run_steps(lbm_domain* dm, int64_t nsteps, hipStream_t st)
 {
     StepArgs a = step_args(dm);
-    if (a.ntiles > dm->L.max_parts)
+    if (!a.pull_slots && a.ntiles > dm->L.max_parts)
         return fail(LBM_EINVAL, "tile %dx%dx%d gives %d tiles, more than the %lld monitor slots", dm->tx, dm->ty,
                     dm->tz, a.ntiles, (long long)dm->L.max_parts);
     // the population stride must cover every slot the layout addresses
