@@ -407,7 +407,7 @@ int lbm_batch_get_schedule(lbm_batch* b, int32_t* tile_policy, int32_t* xcd_orde
  * it).  LBM_EINVAL outside the ranges above.  Synchronises. */
 int lbm_batch_set_schedule(lbm_batch* b, int32_t tile_policy, int32_t xcd_order);
 /* The work-item order alone: 0, 1, or -1 (the default) for chunks while the
- * arena is below 400 MB and plain order above.  Synchronises.  The getter
+ * arena is below 200 MB and plain order above.  Synchronises.  The getter
  * reports the selection and the order in effect. */
 int lbm_batch_set_order(lbm_batch* b, int32_t xcd_order);
 int lbm_batch_get_order(lbm_batch* b, int32_t* selected, int32_t* in_effect);

@@ -1607,11 +1607,12 @@ int batch_plan(lbm_batch* b)
 }
 
 // Items in one contiguous chunk per XCD: on request (order 1), and by default
-// while the arena is cache-sized.  Neighbouring items then meet in one L2 from
-// step to step: sweeps of 4 to 160 ducts below 400 MB ran 3 to 28% faster that
-// way (32 MB FP32 14.0 -> 11.3 us a step, 173 MB FP64 59.6 -> 53.7; 57 MB FP64
-// 20.4 -> 20.9 the one that lost), above 400 MB 0 to 3% slower.
-bool batch_chunks(const lbm_batch* b) { return b->xcd < 0 ? (double)b->L.pdf < 400e6 : b->xcd != 0; }
+// while the arena is below 200 MB.  Neighbouring items then meet in one L2 from
+// step to step.  Sweeps of 4 to 1000 ducts and D2Q9 boxes, chunks over plain
+// order: 0.72 to 0.98 of the time at 8 to 185 MB (42 sweeps, every precision, all
+// faster); 0.96 to 1.05 at 250 to 390 MB, where D2Q9 loses up to 5%; 0.97 to 1.06
+// above.
+bool batch_chunks(const lbm_batch* b) { return b->xcd < 0 ? (double)b->L.pdf < 200e6 : b->xcd != 0; }
 
 // One block per work item, a multiple of 8 in the per-XCD order.
 void batch_set_grid(lbm_batch* b)

@@ -1,6 +1,6 @@
 """GPU tests of the batch's work-item order: what is selected and what is in
 effect, plain order where it is asked for on an arena that the caches hold, and
-arenas just below and above the sizes where the default changes (400 MB: chunks
+arenas just below and above the sizes where the default changes (200 MB: chunks
 to plain order; 512 MiB: streamed local phase), bit for bit against the
 single-domain runs."""
 import numpy as np
@@ -51,7 +51,7 @@ def test_selection_and_effect():
     b.close()
 
 
-@pytest.mark.parametrize("side,mb,effect", [(107, 397, 1), (108, 408, 0), (118, 532, 0), (119, 546, 0)])
+@pytest.mark.parametrize("side,mb,effect", [(85, 199, 1), (86, 206, 0), (118, 532, 0), (119, 546, 0)])
 def test_sizes_where_the_default_changes(side, mb, effect):
     from paper_1610_01388_amd import lbm
     cases = cases_of((side, side, side))
