@@ -440,7 +440,7 @@ int run_steps(lbm_domain* dm, int64_t nsteps, hipStream_t st)
             a.src = dm->pdf;
             a.dst = dm->pdf;
             // the local phase walks backwards (see k_local_slots)
-            a.rev = dm->parity != 0 && dm->d.layout == LBM_COMPACT && (bytes <= 400e6 || bytes > 1e9) ? 1 : 0;
+            a.rev = dm->parity != 0 && dm->d.layout == LBM_COMPACT && bytes <= 400e6 ? 1 : 0;
         }
         const bool mon = dm->mon_k > 0 && (dm->t % dm->mon_k) == 0;
         HIPCHK(launch_step(dm->d.lattice, kernel_op(dm->r) | (a.fallback ? OP_FB : 0), dm->d.precision, pat, mon,

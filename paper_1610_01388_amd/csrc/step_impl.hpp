@@ -676,11 +676,11 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_step_rows(const StepArgs a
 // NT: non-temporal loads and stores, for states larger than the caches
 // (a cache-resident state would only lose its hits).  With rev set (states up
 // to 400 MB) each XCD walks its own one of the pull's eight ranges, backwards:
-// what the pull touched last is still cached (a 382 MB tight medium 715 -> 690
-// us for 4 steps; A/B alternates the direction in the same way, 2 x 179 MB
-// plates 835 -> 771 for 10).  Larger states take the slots in one sequence
-// (eight at a time cost the streamed FP64 phase 4%, FP16 7%; 1% at 500 MB),
-// above 1 GB from the end (0.2 to 0.8% faster there, 1% slower at 550 MB).
+// what the pull touched last is still cached (0.92 to 0.99 of the time at 210 to
+// 400 MB, 22 sizes but two, of 1.00 and 1.035; A/B alternates the direction in the
+// same way).  Larger states take the slots in one sequence (eight at a time cost the
+// streamed FP64 phase 4%, FP16 7%; 1% at 500 MB); from the end it took 0.993 to
+// 1.008 of the time above 1 GB.
 // Monitor partials: one per block.
 template <int LAT, int OP, int PREC, bool MON, bool NT>
 __global__ __launch_bounds__(kMaxBlockThreads) void k_local_slots(const StepArgs a)
@@ -692,10 +692,8 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_local_slots(const StepArgs
     using T = typename Store<PREC>::T;
 
     const int64_t nblk = (a.nfluid + 255) >> 8;
-    const int64_t cb = !a.rev ? (int64_t)blockIdx.x
-                       : NT   ? nblk - 1 - blockIdx.x
-                              : xcd_place(blockIdx.x, a.slot_bpx, 1);
-    if (cb < 0 || cb >= nblk) return;  // whole block leaves together
+    const int64_t cb = !NT && a.rev ? xcd_place(blockIdx.x, a.slot_bpx, 1) : (int64_t)blockIdx.x;
+    if (cb >= nblk) return;  // whole block leaves together
     const int64_t k = cb * 256 + threadIdx.x;
     const bool active = k < a.nfluid;
     const int64_t St = a.S;
