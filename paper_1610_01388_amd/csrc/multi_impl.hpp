@@ -1,7 +1,7 @@
 // multi_impl.hpp -- several time steps per launch for small domains (AA
 // scheme, compact layout), the populations of a tile held in LDS.
 //
-// A per-step kernel on a domain of a few thousand nodes costs 4 to 9 us, most
+// A per-step kernel on a domain of a few thousand nodes costs 4 to 7 us, most
 // of it launch, memory latency and the end-of-kernel write-back; the node
 // update itself is a chain of 1 to 2 us.  Here a block loads a tile and a halo
 // of `steps` nodes once, runs the AA pair (pull, local) in place in LDS with a
@@ -12,12 +12,13 @@
 // launches bring the state back.  A domain of one node per thread of a block
 // stays in one block for any number of steps, in place.
 //
-// In-block time, D3Q19 FP64 IR, 128 x 128 x 4, tile 8 x 8 x 4, 4 steps (us):
-// load 4, steps 3.5 + 2.5 + 2.2 + 1.6 (13, 9, 7, 4 waves: the vector work of
-// the fullest SIMD, then one wave's dependent chain), launch gap 2.5.
-// Per step, per-step kernels -> here: that duct 9.2 -> 4.6 us, the 4 x 64
-// D2Q9 channel 4.3 -> 0.55 (one block), the 80 x 80 D2Q9 PR cylinder cell 4.4 ->
-// 1.95, 400 x 400 D2Q9 IR 10.4 -> 3.5, 63 x 63 x 4 D3Q27 FP32 PR 5.4 -> 4.0.
+// What bounds it: the dependent chain of a node update and the barrier behind it.
+// D3Q19 FP64 IR, 128 x 128 x 4, tile 8 x 8 x 4: a launch of 4 steps takes 19.4 us,
+// with 992 vector instructions a wave and the vector unit 26% busy; the box of
+// 1024 nodes loads 4 and updates 2 nodes per node of the tile.
+// Per step, single steps -> here: that duct 6.7 -> 4.6 us, the 4 x 64 D2Q9
+// channel 3.6 -> 0.55 (one block), an 80 x 80 D2Q9 PR cell 3.8 -> 2.0, 400 x 400
+// D2Q9 IR 5.8 -> 3.4, 63 x 63 x 4 D3Q27 FP32 PR 5.4 -> 4.0.
 //
 // Places in LDS are byte addresses formed without branches: own slot plus the
 // neighbour's offset under the neighbour's fluid bit.

@@ -501,14 +501,17 @@ __device__ __forceinline__ uint32_t add_bit(uint32_t a, uint32_t b, uint64_t mas
 // 2 S (population stride) bytes of storage element below 2^32 (checked on the
 // host; k_step_compact serves larger domains).
 //
-// What bounds it: memory above 512 MB of state; below, the vector unit (FP16
-// 92% busy) and the scalar prologue in front of the first load.  The shifted
-// words come ready from the records, the edge lanes are written with
-// v_writelane, x + 1's slot adds the lane mask's bit, and the tile
-// walk divides by multiplication: FP16 IR 780 -> 629 vector instructions a wave
-// (FP32 PR 888 -> 732, FP64 IR 672 -> 530) and 100 scalar ones fewer.  Packs of
-// porosity 0.75, us a step: 146 x 87 x 144 D3Q27 FP16 40.1 -> 34.0, 96^3 FP32
-// PR 28.2 -> 25.9, 113 x 67 x 58 D3Q19 FP32 10.7 -> 9.5, FP64 1% or less.
+// What bounds it: above 512 MB of state the texture addresser, kept busy by the
+// ragged runs' accesses; below, in FP16 the vector unit (89% busy, the addresser
+// 64%), in FP64 the addresser (78%, vector 24%), and waiting for the first loads in
+// a small domain (113 x 67 x 58 D3Q19 FP32: both 26%).  The shifted words come
+// ready from the records, the edge lanes are written with v_writelane (the
+// intrinsic, which has no builtin, by its assembler name), x + 1's slot adds the
+// lane mask's bit, and the tile walk divides by multiplication: 624 vector and 344
+// scalar instructions a wave for D3Q27 FP16 IR (FP32 PR 748 and 351, FP64 IR 527
+// and 365), 145 vector ones fewer than by lanes.  Packs of porosity 0.75, us a
+// step, with flags by lanes -> so: 146 x 87 x 144 D3Q27 FP16 40.1 -> 34.0, 96^3
+// FP32 PR 28.2 -> 25.9, 113 x 67 x 58 D3Q19 FP32 10.7 -> 9.5, FP64 1% or less.
 // LANES: flags and edges formed per lane as before.  Streamed FP32 and FP16
 // states (above 512 MB) keep it: the 256^3 FP32 and 384^3 FP16 packs ran 1%
 // slower with the short form (2192 -> 2214 and 4307 -> 4345 us for 4 steps),
