@@ -868,6 +868,13 @@ __global__ __launch_bounds__(kMaxBlockThreads) void k_pull_slots(const StepArgs 
             h[i] = decode<PREC>((fl ? A + dn * St : A + db * St)[sl], L::w[i], a.h16_scale);
         }
         if constexpr (has_tau(OP)) tau_prev = (C)((const T*)a.tau)[k];
+        // Every load before the first sum: left alone, the scheduler mixes FP64's
+        // sums by classes into the loads and waits after every fourth one.  No
+        // instruction.  2.5 million slots, us a step, left alone -> so: AA D3Q27 IR
+        // 258 -> 240, PR 271 -> 256, D3Q19 PR 200 -> 183; A/B D3Q27 PR 306 -> 278.
+        // PRI (264 -> 269) and IR in A/B (253 -> 258, a wave less) keep their order.
+        if constexpr (sizeof(S) == 8 && op_base(OP) != OP_PRI && !(PAT == PAT_AB && op_base(OP) == OP_IR))
+            __builtin_amdgcn_sched_barrier(0);
 
         collide_node<LAT, OP, PREC>(h, tau_prev, a.fallback, a.cd, cp, mo, pr, used_fb);
 
