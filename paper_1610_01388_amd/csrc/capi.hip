@@ -159,6 +159,8 @@ struct lbm_domain {
     struct {
         int steps = 0;       // per launch; 0: per-step kernels
         int c[3] = {0, 0, 0};  // tile
+        bool pays[2] = {false, false};  // by the time model: eager, in graphs
+        bool selected = false;          // by the caller
     } multi, multi_set;      // in use; as selected by the caller (steps 0: by the time model, 1: never)
 };
 
@@ -535,7 +537,7 @@ bool multi_fits(const lbm_domain* dm, const int (&c)[3], int steps)
 // loaded, a latency per step (the dependent chain of one node update) and the
 // vector work of the fullest SIMD: its waves times `wave`.  PRI and IRHB iterate
 // per node; they are counted four and three times the work of IR and kept to one
-// round.  multi_scale brings it to measured times.
+// round.  (multi_pays, fitted later and closer, decides whether the best is used.)
 double multi_cost(const lbm_domain* dm, const int (&c)[3], int steps)
 {
     int h[3];
@@ -556,45 +558,50 @@ double multi_cost(const lbm_domain* dm, const int (&c)[3], int steps)
     return ((double)rounds * (rounds > 1 ? 1.15 : 1.0) * t + 3.8 + 0.035 * dm->Q) / steps;
 }
 
-// Measured over modelled time of launches of several steps by operator: 3-D and
-// 2-D in FP32 and FP16, then in FP64; 7% more with solids, 26% less for a domain
-// in one block.  Fitted, like steps_cost, to 2500 timings of D2Q9, D3Q19 and
-// D3Q27 domains of 256 to 10^6 nodes, all operators and precisions, without
-// solids and with 10 and 30%, at rest and in strong motion (in the state that
-// suits several steps least): 90% of the times within 14%.
-double multi_scale(const lbm_domain* dm, bool whole)
+// Whether several steps per launch pay, from two times a step in microseconds, of
+// `steps` of tile c in one launch and of single steps, eager or replayed from a
+// graph (whose launches follow each other sooner).  By operator, in FP32 and FP16
+// and in FP64: latency and vector work (per 256 nodes of the box) of a step in
+// LDS; latency and vector work (per 1024 waves) of a single step.  Fitted to 4200
+// timings of D2Q9, D3Q19 and D3Q27 domains of up to 400 000 nodes, all operators
+// and precisions, with and without solids, eager and in graphs, at rest and in
+// strong motion (profiles/steps_per_launch_times.txt): the ratio of the two is
+// within 5% of the measured one for half of them, 16% for 90%.  Asked for: plans of
+// six steps and more may promise the same time (699 of 702 were faster), four
+// steps 2% less, two steps 4%.
+bool multi_pays(const lbm_domain* dm, const int (&c)[3], int steps, bool replayed)
 {
-    static const double k[4][4] = {{1.05, 1.01, 1.14, 1.19},   // LBM_PR
-                                   {1.02, 0.92, 1.06, 1.09},   // LBM_IR
-                                   {0.93, 1.03, 1.15, 1.44},   // LBM_PRI
-                                   {1.27, 1.68, 1.20, 1.54}};  // LBM_IRHB
-    return k[dm->r.op][(dm->d.precision == LBM_FP64 ? 2 : 0) + (dm->D == 2 ? 1 : 0)] * (dm->Nf < dm->N ? 1.07 : 1.0) *
-           (whole ? 0.74 : 1.0);
-}
+    struct Op {
+        double lat, vec, base, wave;
+    };
+    static const Op table[4][2] = {{{0.895, 0.718, 2.675, 0.310}, {0.364, 1.040, 3.140, 0.403}},   // LBM_PR
+                                   {{0.863, 0.423, 2.322, 0.225}, {0.417, 0.655, 2.706, 0.300}},   // LBM_IR
+                                   {{0.394, 1.639, 3.448, 0.722}, {0.000, 2.735, 4.251, 1.104}},   // LBM_PRI
+                                   {{0.490, 1.737, 4.095, 0.658}, {0.002, 1.938, 3.544, 0.671}}};  // LBM_IRHB
+    const Op& op = table[dm->r.op][dm->d.precision == LBM_FP64 ? 1 : 0];
+    const double Q = dm->Q, es = (double)prec_bytes(dm->d.precision);
+    const bool solids = dm->Nf < dm->N;
 
-// The per-step kernels on a cache-resident domain, microseconds a step: launch
-// and latency, the populations at 6 to 8 TB/s, past 30 MB a step at 4 (3-D) and 9
-// (2-D), and the operator's arithmetic.
-double steps_cost(const lbm_domain* dm)
-{
-    const double mb = 2e-6 * (double)dm->Nf * dm->Q * (double)prec_bytes(dm->d.precision), n = 1e-5 * (double)dm->N;
-    const double op = dm->r.op == LBM_IR    ? 0.0
-                      : dm->r.op == LBM_PR  ? 0.47
-                      : dm->r.op == LBM_PRI ? 1.6 + 0.65 * n
-                                            : 2.65 + 0.75 * n;
-    const bool flat = dm->D == 2;
-    return 2.4 + 0.078 * dm->Q + (flat ? 0.13 : 0.156) * std::min(mb, 30.0) +
-           (flat ? 0.114 : 0.263) * std::max(mb - 30.0, 0.0) + op;
-}
+    int h[3];
+    int64_t M, tiles;
+    multi_box(dm, c, steps, h, M, tiles);
+    const int n = tiles == 1 ? 100 : steps;
+    const double lat = op.lat * (1.0 + 0.081 * (Q - 19.0));
+    const double vec = op.vec * (1.0 + 0.015 * (Q - 19.0)) * (dm->d.precision == LBM_FP16 ? 1.132 : 1.0) * (solids ? 1.031 : 1.0);
+    double t = 2.463e-5 * (double)M * Q * es + (solids ? 0.988e-3 * (double)M : 0.0);
+    for (int s = 1; s <= n; ++s) {
+        int64_t e = 1;
+        for (int a = 0; a < 3; ++a) e *= c[a] + 2 * (h[a] && tiles > 1 ? h[a] - s : 0);
+        t += lat + vec * (double)((e + 255) / 256);
+    }
+    const int64_t rounds = (tiles + dm->cus - 1) / dm->cus;
+    const double several = ((double)rounds * (rounds > 1 ? 1.15 : 1.0) * t + 5.195 + 0.019 * Q + (replayed ? 0.123 : 0.0)) / n;
 
-// Share of the single steps' time that several steps have to promise: the rest
-// covers the models' error, which is larger where a per-node solve's iterations
-// depend on the flow.  Of 907 of those domains, every one with 0.97 or more of the
-// single steps' time but three of 1.01 is left out, and 5% of those below 0.85.
-double multi_promise(const lbm_domain* dm)
-{
-    if (dm->r.op == LBM_PR || dm->r.op == LBM_IR) return 0.9;
-    return dm->D == 3 ? 0.75 : dm->r.op == LBM_PRI ? 0.9 : 0.85;
+    const double mb = 2e-6 * (double)dm->Nf * Q * es;
+    const double waves = (double)dm->L.W * dm->d.ny * dm->d.nz / 1024.0;
+    const double single = op.base + 0.079 * Q + op.wave * (dm->D == 2 ? 1.21 : 1.0) * waves + 0.076 * mb +
+                          0.048 * std::max(mb - 30.0, 0.0) - (replayed ? 0.405 : 0.0);
+    return several < (steps >= 6 ? 1.02 : steps == 4 ? 0.98 : 0.96) * single;
 }
 
 // Choose tile and steps per launch, or none.  Tiles cut the axes evenly into
@@ -603,10 +610,11 @@ double multi_promise(const lbm_domain* dm)
 // caller holds while it fits (a mask with solids takes more LDS per node).
 void plan_multi(lbm_domain* dm)
 {
-    dm->multi.steps = 0;
+    dm->multi = {};
     if (!multi_able(dm) || dm->multi_set.steps == 1) return;
     if (dm->multi_set.steps > 1 && multi_fits(dm, dm->multi_set.c, dm->multi_set.steps)) {
         dm->multi = dm->multi_set;
+        dm->multi.selected = true;
         return;
     }
     const int n[3] = {dm->d.nx, dm->d.ny, dm->d.nz};
@@ -639,7 +647,9 @@ void plan_multi(lbm_domain* dm)
                     }
                 }
             }
-    if (best * multi_scale(dm, plan.steps == kMultiBoxSteps) < multi_promise(dm) * steps_cost(dm)) dm->multi = plan;
+    if (best >= 1e30) return;
+    for (int k = 0; k < 2; ++k) plan.pays[k] = multi_pays(dm, plan.c, plan.steps, k == 1);
+    if (plan.pays[0] || plan.pays[1]) dm->multi = plan;
 }
 
 int launch_multi_steps(lbm_domain* dm, int steps, bool back, hipStream_t st)
@@ -696,8 +706,9 @@ int launch_multi_steps(lbm_domain* dm, int steps, bool back, hipStream_t st)
 bool multi_on(const lbm_domain* dm)
 {
     if (dm->multi.steps == 0) return false;
-    if (dm->multi_set.steps > 1) return true;
-    return default_walk(dm) && dm->pull_form == LBM_PULL_AUTO && (dm->mon_k == 0 || dm->mon_k > 4);
+    if (dm->multi.selected) return true;
+    return dm->multi.pays[dm->graph_steps > 0 ? 1 : 0] && default_walk(dm) && dm->pull_form == LBM_PULL_AUTO &&
+           (dm->mon_k == 0 || dm->mon_k > 4);
 }
 
 // Enqueue nsteps steps: by k_multi where the plan says so (between monitor
@@ -1382,7 +1393,10 @@ int lbm_autotune(lbm_domain* dm, int32_t trial_steps)
     const int keep[3] = {dm->tx, dm->ty, dm->tz};
     const int keep_form = dm->pull_form;
     const int keep_order[2] = {dm->bry, dm->brz};
-    if (dm->multi.steps > 0 && (mon_k == 0 || mon_k > 4) && he == hipSuccess) {
+    default_tile(dm, dm->tx, dm->ty, dm->tz);
+    dm->bry = dm->brz = 0;
+    dm->pull_form = LBM_PULL_AUTO;
+    if (multi_on(dm) && (mon_k == 0 || mon_k > 4) && he == hipSuccess) {
         // several steps per launch, as a long run takes them: whole pairs of
         // launches, or 256 steps of a domain in one block; with records closer
         // than eight of those, whole monitor intervals (two where their length
@@ -1394,9 +1408,6 @@ int lbm_autotune(lbm_domain* dm, int32_t trial_steps)
         const int gap = mon_k < 8 * pair ? mon_k : 0;
         const int unit = gap > 0 ? gap * (1 + gap % 2) : pair;
         const int64_t n = ((int64_t)trial_steps + unit - 1) / unit * unit;
-        default_tile(dm, dm->tx, dm->ty, dm->tz);
-        dm->bry = dm->brz = 0;
-        dm->pull_form = LBM_PULL_AUTO;
         float ms = 0;
         if ((rc = advance(dm, 2 * unit - dm->t % unit, dm->stream, gap)) == LBM_OK &&
             (he = hipEventRecord(e0, dm->stream)) == hipSuccess && (rc = advance(dm, n, dm->stream, gap)) == LBM_OK &&
@@ -1405,9 +1416,12 @@ int lbm_autotune(lbm_domain* dm, int32_t trial_steps)
             best_ms = ms * (float)trial_steps / (float)n;
             best = -3;
         }
-        dm->bry = keep_order[0];
-        dm->brz = keep_order[1];
     }
+    dm->tx = keep[0];
+    dm->ty = keep[1];
+    dm->tz = keep[2];
+    dm->bry = keep_order[0];
+    dm->brz = keep_order[1];
     for (int c = dm->d.layout == LBM_COMPACT ? -1 : 0; c < nc && he == hipSuccess && rc == LBM_OK; ++c) {
         if (c >= 0) {
             const int tx = cand[c][0], ty = cand[c][1], tz = cand[c][2];
