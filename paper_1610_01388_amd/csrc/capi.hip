@@ -567,7 +567,7 @@ double multi_cost(const lbm_domain* dm, const int (&c)[3], int steps)
 // and precisions, with and without solids, eager and in graphs, at rest and in
 // strong motion (profiles/steps_per_launch_times.txt): the ratio of the two is
 // within 5% of the measured one for half of them, 16% for 90%.  Asked for: plans of
-// six steps and more may promise the same time (699 of 702 were faster), four
+// six steps and more may promise the same time (1070 of 1075 were faster), four
 // steps 2% less, two steps 4%.
 bool multi_pays(const lbm_domain* dm, const int (&c)[3], int steps, bool replayed)
 {
