@@ -90,11 +90,13 @@ typedef enum { LBM_COMPACT = 0, LBM_DENSE = 1 } lbm_layout;
  * of solid nodes idle; fastest when most nodes are fluid).  SLOTS runs one
  * thread per fluid slot, 64 consecutive slots per wavefront (every lane
  * busy; fastest when most nodes are solid).  AUTO (default) takes SLOTS
- * when fewer than 45% of the nodes are fluid, else ROWS; and for a small
- * domain (AA, no MRT, no FP64 redo, default tile and tile order) the steps
- * between monitor records are taken several per launch, the populations of a
- * tile held in the local memory of a compute unit and a second copy of them
- * in the work buffer's staging area.  Identical results. */
+ * when fewer than 45% of the nodes are fluid or the rows are so short that
+ * ROWS refuses them, else ROWS; and for a small domain (AA, no MRT, no FP64
+ * redo, default tile and tile order, a monitor interval of 0 or above 4) where
+ * a time model finds it faster, the steps between monitor records are taken
+ * several per launch, the populations of a tile held in the local memory of a
+ * compute unit and a second copy of them in the work buffer's staging area
+ * (lbm_set_steps_per_launch).  Identical results. */
 typedef enum { LBM_PULL_AUTO = 0, LBM_PULL_SLOTS = 1, LBM_PULL_ROWS = 2 } lbm_pull_form;
 
 typedef struct {
